@@ -863,6 +863,13 @@ __global__ void k_gather_steps(const char* tab, size_t slot_bytes, size_t step_o
   if (s < n) out[s] = **reinterpret_cast<long long* const*>(tab + s * slot_bytes + step_off);
 }
 
+// Work-groups of a histogram over at most n particles: two particles per
+// thread for small species, a fixed grid for large ones.
+dim3 hist_grid(long long n) {
+  const long long per = 2ll * kHistThreads;
+  return dim3((unsigned)std::max<long long>(1, std::min<long long>(kHistBlocks, (n + per - 1) / per)));
+}
+
 // ---------------------------------------------------------------- static scratch
 __global__ void k_fill_u64(unsigned long long* p, int n, unsigned long long v) {
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -1260,10 +1267,10 @@ pic_status pic_spectrum_static(pic_run* r, int32_t bins, double e_max, double* h
   hipLaunchKernelGGL(k_fill_u64, dim3((bins + 255) / 256), dim3(256), 0, s, hist, bins, 0ull);
   const double mc2 = r->cfg.mass_ratio * kMec2_MeV;
   if (r->d.prec == PIC_FP32)
-    hipLaunchKernelGGL(k_spectrum<float>, dim3(1024), dim3(256), 0, s, dev<float>(r->sp[1][r->pp]),
+    hipLaunchKernelGGL(k_spectrum<float>, hist_grid(r->n_max[1]), dim3(kHistThreads), 0, s, dev<float>(r->sp[1][r->pp]),
                        r->count + 2 * r->pp + 1, hist, bins, e_max, mc2, (float)(256.0 / r->d.w_ref));
   else
-    hipLaunchKernelGGL(k_spectrum<double>, dim3(1024), dim3(256), 0, s, dev<double>(r->sp[1][r->pp]),
+    hipLaunchKernelGGL(k_spectrum<double>, hist_grid(r->n_max[1]), dim3(kHistThreads), 0, s, dev<double>(r->sp[1][r->pp]),
                        r->count + 2 * r->pp + 1, hist, bins, e_max, mc2, 256.0 / r->d.w_ref);
   HIP_TRY(hipGetLastError());
   // the 64-bit counts land in the caller's array and are converted in place
@@ -1285,13 +1292,12 @@ pic_status pic_spectrum(pic_run* r, int32_t bins, double e_max, double* host_his
   hipStream_t s = S(stream);
   const double mc2 = r->cfg.mass_ratio * kMec2_MeV;
   HIP_TRY(hipMemsetAsync(r->hist, 0, bins * sizeof(unsigned long long), s));
-  const int blocks = 1024;
   if (r->d.prec == PIC_FP32)
-    hipLaunchKernelGGL(k_spectrum<float>, dim3(blocks), dim3(256), 0, s, dev<float>(r->sp[1][r->pp]),
+    hipLaunchKernelGGL(k_spectrum<float>, hist_grid(r->n_max[1]), dim3(kHistThreads), 0, s, dev<float>(r->sp[1][r->pp]),
                        r->count + 2 * r->pp + 1, r->hist, bins, e_max, mc2,
                        (float)(256.0 / r->d.w_ref));
   else
-    hipLaunchKernelGGL(k_spectrum<double>, dim3(blocks), dim3(256), 0, s, dev<double>(r->sp[1][r->pp]),
+    hipLaunchKernelGGL(k_spectrum<double>, hist_grid(r->n_max[1]), dim3(kHistThreads), 0, s, dev<double>(r->sp[1][r->pp]),
                        r->count + 2 * r->pp + 1, r->hist, bins, e_max, mc2, 256.0 / r->d.w_ref);
   HIP_TRY(hipGetLastError());
   std::vector<long long> h(bins);
@@ -1313,10 +1319,10 @@ pic_status pic_friction(pic_run* r, int32_t bins, double log10_lo, double log10_
   HIP_TRY(hipMemsetAsync(out, 0, (bins + 5) * sizeof(double), s));
   const int p = (int)(r->step & 1);
   if (r->d.prec == PIC_FP32)
-    hipLaunchKernelGGL(k_friction<float>, dim3(1024), dim3(256), 0, s, dev<float>(r->sp[0][r->pp]),
+    hipLaunchKernelGGL(k_friction<float>, hist_grid(r->n_max[0]), dim3(kHistThreads), 0, s, dev<float>(r->sp[0][r->pp]),
                        fdev<float>(r, p), r->count + 2 * r->pp, out, bins, log10_lo, log10_hi, r->d.eps);
   else
-    hipLaunchKernelGGL(k_friction<double>, dim3(1024), dim3(256), 0, s, dev<double>(r->sp[0][r->pp]),
+    hipLaunchKernelGGL(k_friction<double>, hist_grid(r->n_max[0]), dim3(kHistThreads), 0, s, dev<double>(r->sp[0][r->pp]),
                        fdev<double>(r, p), r->count + 2 * r->pp, out, bins, log10_lo, log10_hi, r->d.eps);
   HIP_TRY(hipGetLastError());
   std::vector<double> h(bins + 5);
