@@ -1793,9 +1793,12 @@ struct DiagArgs {
   const long long* count;
   FieldsDev<R> f;
   const long long* Ex_int;
-  long long* rho;        // [n + 3] integer charge on nodes (index node + 1), zeroed by caller
-  double* part;          // partials: [2][kDiagPartBlocks] kinetic, [3][kDiagFieldBlocks] fields
+  long long* rho;        // [n + 3] integer charge on nodes (index node + 1): zero on entry, zeroed again
+  double* part;          // partials: [2][kDiagPartBlocks] kinetic, [7][kDiagFieldBlocks]: fields (3),
+                         // tile accumulators (4)
   long long* ipart;      // [kDiagFieldBlocks] gauss max, [2][kDiagPartBlocks] alive counts
+  const double* acc;     // [tiles][4] the push's tile accumulators
+  int tiles;
   int nx;
   double mass[2];
   int Z[2];
@@ -1817,16 +1820,44 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
 
 __device__ __forceinline__ long long wave_sum_ll(long long v) { return wave_sum(v); }
 
+// LDS slots of the integer charge of a diagnostics tile
+constexpr int kDiagSlots = kSortWin + 1;
+
+// Sums of N doubles over the work-group, each in a fixed order; the results
+// are valid on thread 0.  sh holds N * (blockDim.x / 64) doubles.
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N], double* sh) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
+  __syncthreads();
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < N; ++k) sh[k * nw + wid] = v[k];
+  __syncthreads();
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      v[k] = 0.0;
+      for (int w = 0; w < nw; ++w) v[k] += sh[k * nw + w];
+    }
+}
+
 // Kinetic energy (FP64) and integer charge of the particles.  Each block
 // walks sort-sized tiles (blocks of a species stride over its tiles in a
-// fixed order); the charge of a tile is gathered in an LDS window and added
-// to HBM with one atomic per node.
+// fixed order); the charge of a tile is gathered in an LDS window, in up to
+// 16 private copies per node at an odd stride (as the push does: a dense
+// tile's lanes share a cell), and added to HBM with one atomic per node.
+// A tile's values are loaded together with its cells.  Bound by the latency
+// of one tile for small runs (12,800 heated particles: 8.0 us, 28 us with one
+// leader round per distinct cell of a wave) and by HBM for large ones (1e8
+// particles, 24 B of each: 520 us, before 725).
 template <typename R>
 __global__ __launch_bounds__(kDiagThreads) void k_diag_particles(DiagArgs<R> p) {
   static_assert(kDiagThreads == kSortThreads, "diag tiles reuse the sort tiling");
   __shared__ double sh[kDiagThreads / 64];
   __shared__ long long sa[kDiagThreads / 64];
-  __shared__ unsigned long long rw[kSortWin + 1];
+  __shared__ unsigned long long rw[kDiagSlots];
   __shared__ int sm[8];
   const int s = blockIdx.x < kDiagPartBlocks ? 0 : 1;
   const int b = blockIdx.x - s * kDiagPartBlocks;
@@ -1838,60 +1869,58 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_particles(DiagArgs<R> p) 
   for (long long base = (long long)b * kSortTile; base < n;
        base += (long long)kDiagPartBlocks * kSortTile) {
     int cl[kSortPPT];
+    R off[kSortPPT], ux[kSortPPT], uy[kSortPPT], uz[kSortPPT], w[kSortPPT];
 #pragma unroll
     for (int k = 0; k < kSortPPT; ++k) {
       const long long i = base + k * kSortThreads + threadIdx.x;
-      cl[k] = i < n ? sp.cell[i] : kDead;
+      const unsigned ui = (unsigned)(i < n ? i : n - 1);
+      cl[k] = ld(sp.cell, ui);
+      if (i >= n) cl[k] = kDead;
+      off[k] = ld(sp.off, ui);
+      ux[k] = ld(sp.ux, ui);
+      uy[k] = ld(sp.uy, ui);
+      uz[k] = ld(sp.uz, ui);
+      w[k] = ld(sp.w, ui);
     }
     int lo, hi;
     tile_range(cl, lo, hi, sm);
     if (lo > hi) continue;  // block-uniform
     const int W = hi - lo + 2;  // nodes lo .. hi + 1
-    const bool win = W <= kSortWin + 1;
+    int csh = 4;
+    while (csh > 0 && W * ((1 << csh) + 1) > kDiagSlots) --csh;
+    const int P = csh ? (1 << csh) + 1 : 1, copy = lane & ((1 << csh) - 1);
+    const bool win = W * P <= kDiagSlots;
     if (win) {
-      for (int e = threadIdx.x; e < W; e += kSortThreads) rw[e] = 0ull;
+      for (int e = threadIdx.x; e < W * P; e += kSortThreads) rw[e] = 0ull;
       __syncthreads();
     }
-#pragma unroll 4
+#pragma unroll
     for (int k = 0; k < kSortPPT; ++k) {
-      const long long i = base + k * kSortThreads + threadIdx.x;
       const int c = cl[k];
-      const bool valid = c != kDead;
-      long long r0 = 0, r1 = 0;
-      if (valid) {
-        const double ux = sp.ux[i], uy = sp.uy[i], uz = sp.uz[i];
-        const double g = sqrt(1.0 + ux * ux + uy * uy + uz * uz);
-        ke += (double)sp.w[i] * p.mass[s] * (g - 1.0);
-        const int q = (int)(sp.off[i] * R(kTwo24));
-        const int qw = p.Z[s] * (int)rint(sp.w[i] * p.sw);
-        r0 = (long long)qw * (kTwo24 - q);
-        r1 = (long long)qw * q;
-        alive += 1;
-      }
-      // wave-aggregate equal cells, then one add per distinct cell
-      unsigned long long active = __ballot(valid);
-      while (active) {
-        const int leader = __ffsll((long long)active) - 1;
-        const int lc = __shfl(c, leader);
-        const bool mine = valid && c == lc && ((active >> lane) & 1ull);
-        const long long a0 = wave_sum(mine ? r0 : 0ll);
-        const long long a1 = wave_sum(mine ? r1 : 0ll);
-        if (lane == leader) {
-          if (win) {
-            atomicAdd(rw + (lc - lo), (unsigned long long)a0);
-            atomicAdd(rw + (lc - lo) + 1, (unsigned long long)a1);
-          } else {
-            atomicAdd((unsigned long long*)p.rho + lc + 1, (unsigned long long)a0);
-            atomicAdd((unsigned long long*)p.rho + lc + 2, (unsigned long long)a1);
-          }
-        }
-        active &= ~__ballot(mine);
+      if (c == kDead) continue;
+      const double vx = ux[k], vy = uy[k], vz = uz[k];
+      const double g = sqrt(1.0 + vx * vx + vy * vy + vz * vz);
+      ke += (double)w[k] * p.mass[s] * (g - 1.0);
+      const int q = (int)(off[k] * R(kTwo24));
+      const int qw = p.Z[s] * (int)rint(w[k] * p.sw);
+      const long long r0 = (long long)qw * (kTwo24 - q), r1 = (long long)qw * q;
+      alive += 1;
+      if (win) {
+        unsigned long long* x = rw + (c - lo) * P + copy;
+        atomicAdd(x, (unsigned long long)r0);
+        atomicAdd(x + P, (unsigned long long)r1);
+      } else {
+        atomicAdd((unsigned long long*)p.rho + c + 1, (unsigned long long)r0);
+        atomicAdd((unsigned long long*)p.rho + c + 2, (unsigned long long)r1);
       }
     }
     if (win) {
       __syncthreads();
-      for (int e = threadIdx.x; e < W; e += kSortThreads)
-        if (rw[e]) atomicAdd((unsigned long long*)p.rho + lo + e + 1, rw[e]);
+      for (int e = threadIdx.x; e < W; e += kSortThreads) {
+        unsigned long long v = 0ull;
+        for (int k = 0; k < 1 << csh; ++k) v += rw[e * P + k];
+        if (v) atomicAdd((unsigned long long*)p.rho + lo + e + 1, v);
+      }
       __syncthreads();
     }
   }
@@ -1907,97 +1936,119 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_particles(DiagArgs<R> p) 
   }
 }
 
+// Field energies, the Gauss residual, this block's share of the push's tile
+// accumulators (a fixed set of tiles per thread), and the charge cleared for
+// the next diagnostics.
 template <typename R>
 __global__ __launch_bounds__(kDiagThreads) void k_diag_fields(DiagArgs<R> p) {
-  __shared__ double sh[kDiagThreads / 64];
+  __shared__ double sh[7 * (kDiagThreads / 64)];
   __shared__ long long sm[kDiagThreads / 64];
   const int n = p.nx;
-  double ux = 0.0, ue = 0.0, ub = 0.0;
+  double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // U_Ex, U_Et, U_B; tile accumulators
   long long gmax = 0;
   for (int i = blockIdx.x * kDiagThreads + threadIdx.x; i <= n;
        i += kDiagFieldBlocks * kDiagThreads) {
     const double wn = (i == 0 || i == n) ? 0.5 : 1.0;
     const NodeF<R> nv = p.f.N[i];
     const double ey = nv.ey, ez = nv.ez;
-    ue += wn * (ey * ey + ez * ez);
+    v[1] += wn * (ey * ey + ez * ez);
     if (i >= 1) {  // half-node h = i covers cell i-1
       const HalfF<R> hv = p.f.H[i];
       const double ex = hv.ex, by = hv.by, bz = hv.bz;
-      ux += ex * ex;
-      ub += by * by + bz * bz;
+      v[0] += ex * ex;
+      v[2] += by * by + bz * bz;
     }
     if (i >= 1 && i <= n - 1) {
       long long r = p.Ex_int[i + 1] - p.Ex_int[i] - p.rho[i + 1];
       r = r < 0 ? -r : r;
       gmax = r > gmax ? r : gmax;
     }
+    p.rho[i + 1] = 0;
   }
-  const double t0 = block_sum(ux, sh);
-  const double t1 = block_sum(ue, sh);
-  const double t2 = block_sum(ub, sh);
+#pragma unroll 4
+  for (int t = blockIdx.x * kDiagThreads + threadIdx.x; t < p.tiles;
+       t += kDiagFieldBlocks * kDiagThreads) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[3 + k] += p.acc[4 * (size_t)t + k];
+  }
   long long g = gmax;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const long long v = __shfl_xor(g, o);
-    g = v > g ? v : g;
+    const long long x = __shfl_xor(g, o);
+    g = x > g ? x : g;
   }
   if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = g;
-  __syncthreads();
+  block_sums<7>(v, sh);
   if (threadIdx.x == 0) {
     long long m = 0;
     for (int w = 0; w < kDiagThreads / 64; ++w) m = sm[w] > m ? sm[w] : m;
-    const int base = 2 * kDiagPartBlocks;
-    p.part[base + blockIdx.x] = 0.5 * p.dx * t0;
-    p.part[base + kDiagFieldBlocks + blockIdx.x] = 0.5 * p.dx * t1;
-    p.part[base + 2 * kDiagFieldBlocks + blockIdx.x] = 0.5 * p.dx * t2;
+    double* part = p.part + 2 * kDiagPartBlocks + blockIdx.x;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) part[k * kDiagFieldBlocks] = k < 3 ? 0.5 * p.dx * v[k] : v[k];
     p.ipart[blockIdx.x] = m;
   }
 }
 
-// Final reduction in fixed order into the diagnostics record.
+// Final reduction in fixed order into the diagnostics record, with the
+// run's boundary budget, flags and step counter, so that one copy brings
+// everything to the host.
 struct DiagOutDev {
   double U_Ex, U_Et, U_B, K_e, K_i, E_rad, E_esc, n_stiff;
-  long long gauss_int, alive0, alive1;
+  double budget[3];  // E_in, E_out_left, E_out_right
+  long long gauss_int, alive0, alive1, step;
+  int nonfinite;
 };
 
-// fixed-order parallel reduction: thread t sums entries t, t + 256, ...,
-// then a fixed tree over threads
-__device__ __forceinline__ double fixed_sum(const double* x, int n, int stride, int off,
-                                            double* sh) {
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) v += x[(size_t)i * stride + off];
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
+// One work-group; every partial is loaded before the first sum, so the
+// launch is one memory latency and one reduction: 5.5 us (thread 0 adding
+// the counts one after the other, and an LDS tree per sum: 38 us, and 358 us
+// with the 98,000 tile accumulators of 1e8 particles, now summed above).
+__global__ __launch_bounds__(kDiagThreads) void k_diag_final(const double* part, const long long* ipart,
+                                                             const double* budget, const int* flags,
+                                                             const long long* step, DiagOutDev* out) {
+  static_assert(kDiagPartBlocks == 2 * kDiagThreads && kDiagFieldBlocks == kDiagThreads,
+                "one or two partials per thread");
+  constexpr int T = kDiagThreads, NW = T / 64;
+  __shared__ double sh[9 * NW];
+  __shared__ long long si[3][NW];
+  const int t = threadIdx.x;
+  double v[9];
+  v[0] = part[t] + part[T + t];
+  v[1] = part[2 * T + t] + part[3 * T + t];
+#pragma unroll
+  for (int k = 0; k < 7; ++k) v[2 + k] = part[(4 + k) * T + t];
+  long long a0 = ipart[T + t] + ipart[2 * T + t], a1 = ipart[3 * T + t] + ipart[4 * T + t], g = ipart[t];
+  a0 = wave_sum(a0);
+  a1 = wave_sum(a1);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const long long x = __shfl_xor(g, o);
+    g = x > g ? x : g;
   }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
-__global__ __launch_bounds__(256) void k_diag_final(const double* part, const long long* ipart,
-                                                    const double* acc, int tiles,
-                                                    DiagOutDev* out) {
-  __shared__ double sh[256];
-  const int base = 2 * kDiagPartBlocks;
-  DiagOutDev o{};
-  o.K_e = fixed_sum(part, kDiagPartBlocks, 1, 0, sh);
-  o.K_i = fixed_sum(part + kDiagPartBlocks, kDiagPartBlocks, 1, 0, sh);
-  o.U_Ex = fixed_sum(part + base, kDiagFieldBlocks, 1, 0, sh);
-  o.U_Et = fixed_sum(part + base + kDiagFieldBlocks, kDiagFieldBlocks, 1, 0, sh);
-  o.U_B = fixed_sum(part + base + 2 * kDiagFieldBlocks, kDiagFieldBlocks, 1, 0, sh);
-  o.E_rad = fixed_sum(acc, tiles, 4, 0, sh);
-  o.E_esc = fixed_sum(acc, tiles, 4, 1, sh) + fixed_sum(acc, tiles, 4, 2, sh);
-  o.n_stiff = fixed_sum(acc, tiles, 4, 3, sh);
-  if (threadIdx.x == 0) {
-    for (int b = 0; b < kDiagPartBlocks; ++b) {
-      o.alive0 += ipart[kDiagFieldBlocks + b];
-      o.alive1 += ipart[kDiagFieldBlocks + kDiagPartBlocks + b];
+  if ((t & 63) == 0) {
+    si[0][t >> 6] = a0;
+    si[1][t >> 6] = a1;
+    si[2][t >> 6] = g;
+  }
+  block_sums<9>(v, sh);
+  if (t == 0) {
+    DiagOutDev o{};
+    o.K_e = v[0];
+    o.K_i = v[1];
+    o.U_Ex = v[2];
+    o.U_Et = v[3];
+    o.U_B = v[4];
+    o.E_rad = v[5];
+    o.E_esc = v[6] + v[7];
+    o.n_stiff = v[8];
+    for (int w = 0; w < NW; ++w) {
+      o.alive0 += si[0][w];
+      o.alive1 += si[1][w];
+      o.gauss_int = si[2][w] > o.gauss_int ? si[2][w] : o.gauss_int;
     }
-    for (int b = 0; b < kDiagFieldBlocks; ++b)
-      o.gauss_int = ipart[b] > o.gauss_int ? ipart[b] : o.gauss_int;
+    for (int k = 0; k < 3; ++k) o.budget[k] = budget[k];
+    o.step = *step;
+    o.nonfinite = flags[0];
     *out = o;
   }
 }
@@ -2008,9 +2059,9 @@ __global__ __launch_bounds__(256) void k_diag_final(const double* part, const lo
 // work-group adds its non-zero bins to HBM once.  Cold or bunched particles
 // fall into a few bins, and one global atomic per particle then queues on a
 // few addresses: 12 ns per proton (600 ms for 5e7 cold ones; in this form
-// under 1 ms, the time of streaming 20 B each).  The friction histogram of
-// 1e6 electrons took 2.60 ms, the spectrum of 1e6 bunched protons 2.05 ms;
-// with the budget read the three now take 0.28 ms.  Histograms that do not fit keep global atomics, with one
+// 0.17 ms, the time of streaming 20 B each).  The friction histogram of
+// 1e6 electrons went from 2.60 ms to 46 us, the spectrum of 1e6 bunched
+// protons from 2.05 ms to 27 us.  Histograms that do not fit keep global atomics, with one
 // add for a wave whose lanes all hit the same bin.
 constexpr int kHistThreads = 512;
 constexpr int kHistSlots = 4096;   // 8-byte LDS slots: 32 KB, four work-groups per CU

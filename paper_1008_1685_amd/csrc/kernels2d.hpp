@@ -1097,9 +1097,14 @@ struct Diag2Args {
   const long long* count;
   Fields2Dev<R> f;
   const long long* cont;
-  long long* rho;       // [(nx + 1) ny] integer charge of the particles, zeroed by the caller
-  double* part;         // [6][k2DiagBlocks]: K_e, K_i, U_Ex, U_Et, U_B, gauss max
+  long long* rho;       // [(nx + 1) ny] integer charge of the particles: zero on entry (the
+                        // fields pass zeroes it again)
+  double* part;         // [13][k2DiagBlocks]: K_e, K_i, U_Ex, U_Et, U_B, tile accumulators (4),
+                        // boundary energies (3), gauss max
   long long* ipart;     // [3][k2DiagBlocks]: alive e, alive i, continuity max
+  const double* acc;    // [tiles][4] the push's tile accumulators
+  const double* flux;   // [3][ny] boundary energies per row
+  int tiles;
   int nx, ny, ysh;
   double mass[2];
   int Z[2];
@@ -1107,32 +1112,148 @@ struct Diag2Args {
   double dx, srho;      // integer charge -> density
 };
 
-// kinetic energy, alive counts and the integer charge 2 qw S_x S_y
+// kinetic energy, alive counts and the integer charge 2 qw S_x S_y.  Each
+// block walks sort-sized tiles; the cell sort keeps a tile's particles in a
+// compact patch, so its charge is gathered in an LDS box over the patch (the
+// columns and the arc of periodic rows its cells touch, in up to eight
+// private copies at an odd stride) and goes to HBM with one atomic per node.
+// Tiles that do not fit add to HBM directly.  8.4e6 particles: 0.11 ms,
+// against 2.8 ms with four global atomics per particle and 39 us for
+// streaming their 28 B.
+constexpr int k2DiagSlots = 4096;
+
 template <typename R>
 __global__ __launch_bounds__(256) void k_diag2_particles(Diag2Args<R> p) {
+  static_assert(kSortThreads == 256, "diagnostics walk the sort's tiles");
   __shared__ double sh[4];
+  __shared__ unsigned long long box[k2DiagSlots];
+  __shared__ int s_red[4][4];
+  __shared__ int s_jref;
   const int s = blockIdx.x < k2DiagBlocks ? 0 : 1;
   const int b = blockIdx.x - s * k2DiagBlocks;
   const long long n = p.count[s];
   const SpeciesDev<R> sp = p.sp[s];
-  const int ymask = (1 << p.ysh) - 1, ny = p.ny;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int ymask = (1 << p.ysh) - 1, ny = p.ny, half = ny >> 1;
+  unsigned long long* rho = (unsigned long long*)p.rho;
   double ke = 0.0;
   long long alive = 0;
-  for (long long i = (long long)b * 256 + threadIdx.x; i < n; i += (long long)k2DiagBlocks * 256) {
-    const int c = sp.cell[i];
-    if (c == kDead) continue;
-    const double ux = sp.ux[i], uy = sp.uy[i], uz = sp.uz[i];
-    ke += (double)sp.w[i] * p.mass[s] * (sqrt(1.0 + ux * ux + uy * uy + uz * uz) - 1.0);
-    alive += 1;
-    const int ix = c >> p.ysh, iy = c & ymask, iy1 = iy + 1 == ny ? 0 : iy + 1;
-    const long long qx = (long long)(sp.off[i] * R(k2One)), qy = (long long)(sp.oy[i] * R(k2One));
-    const long long qw = 2ll * p.Z[s] * (long long)rint(sp.w[i] * p.sw);
-    unsigned long long* r = (unsigned long long*)p.rho;
-    const size_t c0 = (size_t)ix * ny, c1 = c0 + ny;
-    atomicAdd(r + c0 + iy, (unsigned long long)(qw * (k2One - qx) * (k2One - qy)));
-    atomicAdd(r + c0 + iy1, (unsigned long long)(qw * (k2One - qx) * qy));
-    atomicAdd(r + c1 + iy, (unsigned long long)(qw * qx * (k2One - qy)));
-    atomicAdd(r + c1 + iy1, (unsigned long long)(qw * qx * qy));
+  for (long long base = (long long)b * kSortTile; base < n; base += (long long)k2DiagBlocks * kSortTile) {
+    int cl[kSortPPT];
+    R ox[kSortPPT], oy[kSortPPT], ux[kSortPPT], uy[kSortPPT], uz[kSortPPT], w[kSortPPT];
+#pragma unroll
+    for (int k = 0; k < kSortPPT; ++k) {
+      const long long i = base + k * kSortThreads + tid;
+      const unsigned ui = (unsigned)(i < n ? i : n - 1);
+      cl[k] = ld(sp.cell, ui);
+      if (i >= n) cl[k] = kDead;
+      ox[k] = ld(sp.off, ui);
+      oy[k] = ld(sp.oy, ui);
+      ux[k] = ld(sp.ux, ui);
+      uy[k] = ld(sp.uy, ui);
+      uz[k] = ld(sp.uz, ui);
+      w[k] = ld(sp.w, ui);
+    }
+    // the tile's rows as an arc around the first live particle of thread 0
+    if (tid == 0) {
+      int jr = 0;
+#pragma unroll
+      for (int k = kSortPPT - 1; k >= 0; --k)
+        if (cl[k] != kDead) jr = cl[k] & ymask;
+      s_jref = jr;
+    }
+    __syncthreads();  // (also: the previous tile's box has been flushed)
+    const int jref = s_jref;
+    int xmn = INT_MAX, xmx = INT_MIN, dmn = INT_MAX, dmx = INT_MIN;
+#pragma unroll
+    for (int k = 0; k < kSortPPT; ++k) {
+      const int c = cl[k];
+      if (c != kDead) {
+        const int x = c >> p.ysh;
+        int d = (c & ymask) - jref;
+        d += d < -half ? ny : 0;
+        d -= d >= ny - half ? ny : 0;
+        xmn = min(xmn, x);
+        xmx = max(xmx, x);
+        dmn = min(dmn, d);
+        dmx = max(dmx, d);
+      }
+    }
+    xmn = wave_min_dpp(xmn);
+    xmx = wave_max_dpp(xmx);
+    dmn = wave_min_dpp(dmn);
+    dmx = wave_max_dpp(dmx);
+    if (lane == 0) {
+      s_red[0][wid] = xmn;
+      s_red[1][wid] = xmx;
+      s_red[2][wid] = dmn;
+      s_red[3][wid] = dmx;
+    }
+    __syncthreads();
+    xmn = min(min(s_red[0][0], s_red[0][1]), min(s_red[0][2], s_red[0][3]));
+    xmx = max(max(s_red[1][0], s_red[1][1]), max(s_red[1][2], s_red[1][3]));
+    dmn = min(min(s_red[2][0], s_red[2][1]), min(s_red[2][2], s_red[2][3]));
+    dmx = max(max(s_red[3][0], s_red[3][1]), max(s_red[3][2], s_red[3][3]));
+    if (xmn > xmx) continue;  // every particle of the tile was removed (block-uniform)
+    const int BX = xmx - xmn + 2, span = dmx - dmn + 2;
+    const int BY = span < ny ? span : ny;
+    int jb = span < ny ? jref + dmn : 0;
+    jb += jb < 0 ? ny : 0;
+    jb -= jb >= ny ? ny : 0;
+    const long long slots = (long long)BX * BY;
+    const bool win = slots < k2DiagSlots;
+    int nc = 8;
+    const int S = win ? (int)slots : 1, CS = S | 1;
+    while (nc > 1 && CS * nc > k2DiagSlots) nc >>= 1;
+    unsigned long long* mine = box + (lane & (nc - 1)) * CS;
+    if (win) {
+      for (int e = tid; e < CS * nc; e += 256) box[e] = 0ull;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kSortPPT; ++k) {
+      const int c = cl[k];
+      if (c == kDead) continue;
+      const double vx = ux[k], vy = uy[k], vz = uz[k];
+      ke += (double)w[k] * p.mass[s] * (sqrt(1.0 + vx * vx + vy * vy + vz * vz) - 1.0);
+      alive += 1;
+      const int ix = c >> p.ysh, iy = c & ymask;
+      const long long qx = (long long)(ox[k] * R(k2One)), qy = (long long)(oy[k] * R(k2One));
+      const long long qw = 2ll * p.Z[s] * (long long)rint(w[k] * p.sw);
+      const unsigned long long t00 = (unsigned long long)(qw * (k2One - qx) * (k2One - qy)),
+                               t01 = (unsigned long long)(qw * (k2One - qx) * qy),
+                               t10 = (unsigned long long)(qw * qx * (k2One - qy)),
+                               t11 = (unsigned long long)(qw * qx * qy);
+      if (win) {
+        int r = iy - jb;
+        r += r < 0 ? ny : 0;
+        const int r1 = r + 1 == ny ? 0 : r + 1, c0 = (ix - xmn) * BY;
+        atomicAdd(mine + c0 + r, t00);
+        atomicAdd(mine + c0 + r1, t01);
+        atomicAdd(mine + c0 + BY + r, t10);
+        atomicAdd(mine + c0 + BY + r1, t11);
+      } else {
+        const int iy1 = iy + 1 == ny ? 0 : iy + 1;
+        const size_t c0 = (size_t)ix * ny, c1 = c0 + ny;
+        atomicAdd(rho + c0 + iy, t00);
+        atomicAdd(rho + c0 + iy1, t01);
+        atomicAdd(rho + c1 + iy, t10);
+        atomicAdd(rho + c1 + iy1, t11);
+      }
+    }
+    if (win) {
+      __syncthreads();
+      for (int e = tid; e < S; e += 256) {
+        unsigned long long v = 0ull;
+        for (int k = 0; k < nc; ++k) v += box[k * CS + e];
+        if (v) {
+          const int cx = e / BY, r = e - cx * BY;
+          int gy = jb + r;
+          gy -= gy >= ny ? ny : 0;
+          atomicAdd(rho + (size_t)(xmn + cx) * ny + gy, v);
+        }
+      }
+    }
   }
   const double t = block_sum(ke, sh);
   __shared__ long long sa[4];
@@ -1147,62 +1268,71 @@ __global__ __launch_bounds__(256) void k_diag2_particles(Diag2Args<R> p) {
 
 // field energies, Gauss residual from the fields and the particles' charge,
 // and the largest difference between that charge and the one the current
-// carried, over interior nodes (exact integers: expect 0)
+// carried, over interior nodes (exact integers: expect 0); this block's
+// share of the tile accumulators and of the boundary rows; and the charge
+// cleared for the next diagnostics
 template <typename R>
 __global__ __launch_bounds__(256) void k_diag2_fields(Diag2Args<R> p) {
-  __shared__ double sh[4];
+  __shared__ double sh[10 * 4];
   __shared__ long long sm[4];
-  const int ny = p.ny, n = p.nx;
-  double ux = 0.0, ue = 0.0, ub = 0.0, gmax = 0.0;
+  __shared__ double sg[4];
+  const unsigned ny = (unsigned)p.ny;
+  const int n = p.nx;
+  double v[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, gmax = 0.0;
   long long cmax = 0;
-  const long long tot = (long long)(n + 2) * ny;
-  for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < tot;
-       t += (long long)k2DiagBlocks * 256) {
-    const int X = (int)(t / ny), j = (int)(t - (long long)X * ny);
+  const unsigned tot = (unsigned)(n + 2) * ny;  // (the grid's keys fit 31 bits)
+  const unsigned t0 = blockIdx.x * 256 + threadIdx.x;
+  for (unsigned t = t0; t < tot; t += k2DiagBlocks * 256) {
+    const int X = (int)(t / ny), j = (int)(t - (unsigned)X * ny);
     const size_t c = (size_t)X * ny;
     if (X <= n) {
       const double wn = (X == 0 || X == n) ? 0.5 : 1.0;
       const NH<R> e = p.f.nh[c + j];
       const double ey = e.ey, ez = p.f.ez[c + j], bxv = e.bx;
-      ue += wn * (ey * ey + ez * ez);
-      ub += wn * bxv * bxv;
+      v[1] += wn * (ey * ey + ez * ez);
+      v[2] += wn * bxv * bxv;
+      const long long rho = p.rho[c + j];
+      p.rho[c + j] = 0;
       if (X >= 1 && X <= n - 1) {
         // interior nodes: a particle removed at an x end leaves part of its
         // last shape on the end node, which the current never takes away
-        long long dc = p.cont[c + j] - p.rho[c + j];
+        long long dc = p.cont[c + j] - rho;
         dc = dc < 0 ? -dc : dc;
         cmax = dc > cmax ? dc : cmax;
-        const int jm = j == 0 ? ny - 1 : j - 1;
+        const unsigned jm = j == 0 ? ny - 1 : j - 1;
         const double divE = ((double)p.f.hn[c + ny + j].ex - (double)p.f.hn[c + j].ex) / p.dx +
                             ((double)e.ey - (double)p.f.nh[c + jm].ey) / p.dx;
-        const double r = fabs(divE - (double)p.rho[c + j] * p.srho);
+        const double r = fabs(divE - (double)rho * p.srho);
         gmax = r > gmax ? r : gmax;
       }
     }
     if (X >= 1 && X <= n) {
       const HN<R> h = p.f.hn[c + j];
       const double exv = h.ex, byv = h.by, bzv = p.f.bz[c + j];
-      ux += exv * exv;
-      ub += byv * byv + bzv * bzv;
+      v[0] += exv * exv;
+      v[2] += byv * byv + bzv * bzv;
     }
   }
-  const double a2 = 0.5 * p.dx * p.dx;
-  const double t0 = block_sum(ux, sh), t1 = block_sum(ue, sh), t2 = block_sum(ub, sh);
+  for (unsigned t = t0; t < (unsigned)p.tiles; t += k2DiagBlocks * 256)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[3 + k] += p.acc[4 * (size_t)t + k];
+  for (unsigned t = t0; t < ny; t += k2DiagBlocks * 256)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[7 + k] += p.flux[(size_t)k * ny + t];
   double g = gmax;
   long long cm = cmax;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const double v = __shfl_xor(g, o);
-    g = v > g ? v : g;
+    const double x = __shfl_xor(g, o);
+    g = x > g ? x : g;
     const long long w = __shfl_xor(cm, o);
     cm = w > cm ? w : cm;
   }
-  __shared__ double sg[4];
   if ((threadIdx.x & 63) == 0) {
     sg[threadIdx.x >> 6] = g;
     sm[threadIdx.x >> 6] = cm;
   }
-  __syncthreads();
+  block_sums<10>(v, sh);
   if (threadIdx.x == 0) {
     double gm = 0.0;
     long long m = 0;
@@ -1210,42 +1340,74 @@ __global__ __launch_bounds__(256) void k_diag2_fields(Diag2Args<R> p) {
       gm = sg[w] > gm ? sg[w] : gm;
       m = sm[w] > m ? sm[w] : m;
     }
-    p.part[2 * k2DiagBlocks + blockIdx.x] = a2 * t0;
-    p.part[3 * k2DiagBlocks + blockIdx.x] = a2 * t1;
-    p.part[4 * k2DiagBlocks + blockIdx.x] = a2 * t2;
-    p.part[5 * k2DiagBlocks + blockIdx.x] = gm;
+    const double a2 = 0.5 * p.dx * p.dx;
+    double* part = p.part + 2 * k2DiagBlocks + blockIdx.x;
+#pragma unroll
+    for (int k = 0; k < 10; ++k) part[k * k2DiagBlocks] = k < 3 ? a2 * v[k] : v[k];
+    part[10 * k2DiagBlocks] = gm;
     p.ipart[2 * k2DiagBlocks + blockIdx.x] = m;
   }
 }
 
 struct Diag2OutDev {
   double U_Ex, U_Et, U_B, K_e, K_i, E_rad, E_esc, n_stiff, gauss, E_in, E_ol, E_or;
-  long long cont_max, alive0, alive1;
+  long long cont_max, alive0, alive1, step;
+  int nonfinite;
 };
 
+// One work-group, every partial loaded before the first sum (as in 1D); the
+// flags and the step counter ride along, so that one copy brings everything
 __global__ __launch_bounds__(256) void k_diag2_final(const double* part, const long long* ipart,
-                                                     const double* acc, int tiles,
-                                                     const double* flux, int ny, Diag2OutDev* out) {
-  __shared__ double sh[256];
-  Diag2OutDev o{};
-  o.K_e = fixed_sum(part, k2DiagBlocks, 1, 0, sh);
-  o.K_i = fixed_sum(part + k2DiagBlocks, k2DiagBlocks, 1, 0, sh);
-  o.U_Ex = fixed_sum(part + 2 * k2DiagBlocks, k2DiagBlocks, 1, 0, sh);
-  o.U_Et = fixed_sum(part + 3 * k2DiagBlocks, k2DiagBlocks, 1, 0, sh);
-  o.U_B = fixed_sum(part + 4 * k2DiagBlocks, k2DiagBlocks, 1, 0, sh);
-  o.E_rad = fixed_sum(acc, tiles, 4, 0, sh);
-  o.E_esc = fixed_sum(acc, tiles, 4, 1, sh) + fixed_sum(acc, tiles, 4, 2, sh);
-  o.n_stiff = fixed_sum(acc, tiles, 4, 3, sh);
-  o.E_in = fixed_sum(flux, ny, 1, 0, sh);
-  o.E_ol = fixed_sum(flux + ny, ny, 1, 0, sh);
-  o.E_or = fixed_sum(flux + 2 * ny, ny, 1, 0, sh);
-  if (threadIdx.x == 0) {
-    for (int b = 0; b < k2DiagBlocks; ++b) {
-      o.alive0 += ipart[b];
-      o.alive1 += ipart[k2DiagBlocks + b];
-      o.cont_max = ipart[2 * k2DiagBlocks + b] > o.cont_max ? ipart[2 * k2DiagBlocks + b] : o.cont_max;
-      o.gauss = part[5 * k2DiagBlocks + b] > o.gauss ? part[5 * k2DiagBlocks + b] : o.gauss;
+                                                     const int* flags, const long long* step,
+                                                     Diag2OutDev* out) {
+  static_assert(k2DiagBlocks == 512, "two partials per thread");
+  __shared__ double sh[12 * 4];
+  __shared__ long long si[3][4];
+  __shared__ double sg[4];
+  const int t = threadIdx.x;
+  double v[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) v[k] = part[k * 512 + t] + part[k * 512 + 256 + t];
+  double g = fmax(part[12 * 512 + t], part[12 * 512 + 256 + t]);
+  long long a0 = ipart[t] + ipart[256 + t], a1 = ipart[512 + t] + ipart[768 + t];
+  const long long c0 = ipart[1024 + t], c1 = ipart[1280 + t];
+  long long cm = c0 > c1 ? c0 : c1;
+  a0 = wave_sum(a0);
+  a1 = wave_sum(a1);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    g = fmax(g, __shfl_xor(g, o));
+    const long long w = __shfl_xor(cm, o);
+    cm = w > cm ? w : cm;
+  }
+  if ((t & 63) == 0) {
+    si[0][t >> 6] = a0;
+    si[1][t >> 6] = a1;
+    si[2][t >> 6] = cm;
+    sg[t >> 6] = g;
+  }
+  block_sums<12>(v, sh);
+  if (t == 0) {
+    Diag2OutDev o{};
+    o.K_e = v[0];
+    o.K_i = v[1];
+    o.U_Ex = v[2];
+    o.U_Et = v[3];
+    o.U_B = v[4];
+    o.E_rad = v[5];
+    o.E_esc = v[6] + v[7];
+    o.n_stiff = v[8];
+    o.E_in = v[9];
+    o.E_ol = v[10];
+    o.E_or = v[11];
+    for (int w = 0; w < 4; ++w) {
+      o.alive0 += si[0][w];
+      o.alive1 += si[1][w];
+      o.cont_max = si[2][w] > o.cont_max ? si[2][w] : o.cont_max;
+      o.gauss = fmax(o.gauss, sg[w]);
     }
+    o.step = *step;
+    o.nonfinite = flags[0];
     *out = o;
   }
 }

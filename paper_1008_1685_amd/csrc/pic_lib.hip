@@ -220,7 +220,7 @@ void carve(pic_run* r, Carver& cv) {
     r->cursor[s] = cv.take<int>(d.nx + 1);
   }
   r->rho = cv.take<long long>(d.nx + 3);
-  r->part = cv.take<double>(2 * kDiagPartBlocks + 3 * kDiagFieldBlocks);
+  r->part = cv.take<double>(2 * kDiagPartBlocks + 7 * kDiagFieldBlocks);
   r->ipart = cv.take<long long>(kDiagFieldBlocks + 2 * kDiagPartBlocks);
   r->dout = cv.take<DiagOutDev>(1);
   r->hist = cv.take<unsigned long long>(kMaxSpectrumBins);
@@ -594,6 +594,8 @@ pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   p.rho = r->rho;
   p.part = r->part;
   p.ipart = r->ipart;
+  p.acc = r->acc;
+  p.tiles = r->tiles_max;
   p.nx = d.nx;
   p.mass[0] = 1.0;
   p.mass[1] = r->cfg.mass_ratio;
@@ -601,20 +603,13 @@ pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   p.Z[1] = 1;
   p.sw = (R)(256.0 / d.w_ref);
   p.dx = d.dx;
-  HIP_TRY(hipMemsetAsync(r->rho, 0, sizeof(long long) * (d.nx + 3), st));
   hipLaunchKernelGGL(k_diag_particles<R>, dim3(2 * kDiagPartBlocks), dim3(kDiagThreads), 0, st, p);
   hipLaunchKernelGGL(k_diag_fields<R>, dim3(kDiagFieldBlocks), dim3(kDiagThreads), 0, st, p);
-  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, st, r->part, r->ipart, r->acc,
-                     r->tiles_max, r->dout);
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagThreads), 0, st, r->part, r->ipart, r->budget,
+                     r->flags, r->step_dev, r->dout);
   HIP_TRY(hipGetLastError());
   DiagOutDev o;
-  double budget[4];
-  int flags[4];
-  long long step_dev = 0;
   HIP_TRY(hipMemcpyAsync(&o, r->dout, sizeof(o), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(budget, r->budget, sizeof(budget), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(flags, r->flags, sizeof(flags), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&step_dev, r->step_dev, sizeof(step_dev), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   std::memset(out, 0, sizeof(*out));
   out->step = r->step;
@@ -627,16 +622,16 @@ pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   out->K_e = o.K_e;
   out->K_i = o.K_i;
   out->E_rad = o.E_rad;
-  out->E_in = budget[0];
-  out->E_out_left = budget[1];
-  out->E_out_right = budget[2];
+  out->E_in = o.budget[0];
+  out->E_out_left = o.budget[1];
+  out->E_out_right = o.budget[2];
   out->E_esc = o.E_esc;
   out->gauss_int = o.gauss_int;
   out->gauss = (double)o.gauss_int * d.w_ref * std::ldexp(1.0, -32) / d.dx;
   out->n_stiff = (int64_t)o.n_stiff;
-  out->nonfinite = flags[0] != 0;
+  out->nonfinite = o.nonfinite != 0;
   finish_balance(out);
-  if (step_dev != r->step)
+  if (o.step != r->step)
     return fail(PIC_EHIP, "device step counter disagrees with the host (lost launch?)");
   if (out->nonfinite) return fail(PIC_ENONFINITE, "a particle momentum became non-finite");
   return PIC_OK;
