@@ -352,10 +352,11 @@ pic_status pic_timing_read(struct pic_run* run, double ms[3], int64_t launches[3
  * Serving: continuous batching of independent runs (laser-foil requests of
  * uneven size).  A batch keeps a device table of up to max_slots resident
  * runs and advances all of them with the same launches: per quantum
- * (= the runs' sort_interval steps) one sort stage (hist, scan, scatter) and
- * then, per step, one push-deposit and one field launch whose work-groups
- * are spread over the runs' tiles (the field launch also advances each
- * run's step counter), or, in the persistent form (pic_batch_set_persistent),
+ * (= the runs' sort_interval steps) one sort stage (hist, scan, scatter), a
+ * push-deposit launch, then one launch per step that advances the fields of
+ * that step and pushes the next, and a last field launch (which also
+ * advances each run's step counter), their work-groups spread over the runs'
+ * tiles, or, in the persistent form (pic_batch_set_persistent),
  * one launch that runs all the quantum's steps with grid-wide barriers
  * between the passes.  Each run derives its buffer
  * parities, sort schedule and laser clock from its own device step counter,
@@ -423,9 +424,9 @@ pic_status pic_batch_poll_wait(pic_batch* b, int64_t* steps);
  * them to read their state).  Blocking. */
 pic_status pic_batch_drain(pic_batch* b, int64_t* quanta, void* stream);
 
-/* Choose how a quantum's steps are launched: on = 0 (default), one
- * push-deposit and one field launch per step, 2 x quantum launches after the
- * sort; on = 1, one persistent launch per quantum whose work-groups (as many
+/* Choose how a quantum's steps are launched: on = 0 (default), one launch
+ * per step (a step's field advance with the next step's push-deposit) and
+ * one more, quantum + 1 launches after the sort; on = 1, one persistent launch per quantum whose work-groups (as many
  * as the work needs, no more than fit the device at once) loop over the
  * push tiles and then the field chunks of every run, with a grid-wide
  * barrier after each pass, and advance the step counters once at the end.

@@ -113,7 +113,11 @@ struct PushArgs {
   const long long* count;        // [2] particles per species as of the last sort
   int tiles0;                    // work-groups of species 0
   FieldsDev<R> f;                // E^n, B^n
-  unsigned long long* J[3];      // Jx (half-nodes), Jy, Jz (nodes, index node+1)
+  unsigned long long* J;         // currents [3 buffers][Jx (half-nodes), Jy, Jz (nodes, index node+1)][jstride]
+  unsigned jstride;
+  int jfix;                      // the buffer of this step's current, or -1: step mod 3
+  const long long* step;         // device step counter (read when jfix < 0)
+  int cap;                       // entries of the particle arrays
   double* acc;                   // [tile][4] cumulative: E_rad, E_esc_e, E_esc_i, n_stiff
   int* flags;                    // [0]: non-finite seen
   int nx;
@@ -141,6 +145,20 @@ struct PushArgs {
 };
 
 // ---------------------------------------------------------------- helpers
+// A launch's arguments (or a table no kernel writes) as constant memory, read
+// where they are needed.  Taken by value, the push kernels' arguments can be
+// split into scalars loaded at the kernel's entry, of which there are more
+// than scalar registers: 40 to 180 of them were then spilled into lanes of
+// vector registers.
+template <typename T>
+__device__ __forceinline__ const T& constant_ref(const T* p) {
+  return *(const T*)(const __attribute__((address_space(4))) T*)p;
+}
+template <typename T>
+__device__ __forceinline__ const T& kernel_args() {
+  return *(const T*)(const __attribute__((address_space(4))) T*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 // Approximate (about 1 ulp) reciprocal, reciprocal square root and square
 // root for the Boris and RR arithmetic; the contract lines use IEEE ops.
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
@@ -541,16 +559,16 @@ __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez
 
 // All loads of one particle are independent of each other, so a thread keeps
 // several particles' loads in flight while it computes an earlier one.
-// Past the end of the species (i >= n, last tile only) the loads read
-// particle n - 1 instead, so that they need no branch, and the particle is
-// marked removed.  n >= 1.
+// Past the end of the species (i >= n, last tile only) the loads need no
+// branch, and the particle is marked removed; the address is held to the
+// arrays' capacity, not to n, so that the first loads of a work-group do not
+// wait for the particle count.
 template <typename R, bool COMP>
-__device__ __forceinline__ PData<R> load_particle(const SpeciesDev<R>& sp, int i, int n) {
+__device__ __forceinline__ PData<R> load_particle(const SpeciesDev<R>& sp, int i, int n, int cap) {
   PData<R> d;
-  const bool in = i < n;
-  const unsigned ui = (unsigned)(in ? i : n - 1);
+  const unsigned ui = (unsigned)min(i, cap - 1);
   d.c = ld(sp.cell, ui);
-  if (!in) d.c = kDead;
+  if (i >= n) d.c = kDead;
   d.o = ld(sp.off, ui);
   d.ux = ld(sp.ux, ui);
   d.uy = ld(sp.uy, ui);
@@ -585,6 +603,28 @@ __device__ __forceinline__ Gath<R> gather_issue(const FieldsDev<R>& f, const PDa
   g.n1 = ld(f.N, uc + 1);
   g.h0 = ld(f.H, h);
   g.h1 = ld(f.H, h + 1);
+  return g;
+}
+
+// The fields of a tile's cells held in LDS: nodes and half-nodes c0 .. c0 +
+// len - 1, of which cell c reads nodes c, c + 1 and half-nodes c .. c + 2.
+template <typename R>
+struct StageF {
+  const HalfF<R>* H;
+  const NodeF<R>* N;
+  int c0, len;
+};
+
+template <typename R>
+__device__ __forceinline__ Gath<R> gather_staged(const StageF<R>& f, const PData<R>& pd) {
+  // (a removed particle, or one outside the range: any entry)
+  const int e = min(max(pd.c - f.c0, 0), f.len - 3);
+  const int h = e + (pd.o + R(0.5) >= R(1));
+  Gath<R> g;
+  g.n0 = f.N[e];
+  g.n1 = f.N[e + 1];
+  g.h0 = f.H[h];
+  g.h1 = f.H[h + 1];
   return g;
 }
 
@@ -661,11 +701,359 @@ __device__ __forceinline__ void push_particle(const PushArgs<R>& a, const Specie
   }
 }
 
+// ---------------------------------------------------------------- fields
+template <typename R>
+struct FieldArgs {
+  FieldsDev<R> in, out;           // E^n, B^n -> E^{n+1}, B^{n+1}
+  unsigned long long* J;          // currents, as in PushArgs
+  unsigned jstride;
+  int jfix;                       // buffer of this step's current, or -1: step mod 3
+  const long long* Ex_in;         // integrals of the charge flux at n and n + 1
+  long long* Ex_out;
+  double* budget;                 // [0] E_in, [1] E_out_left, [2] E_out_right
+  // incident (E_y, E_z) at t_{n+1/2}, in entry n & 1: the field pass of step
+  // n - 1 (k_incident for a first step) leaves it, so that no pass waits for
+  // the FP64 sines and no push tile has to hold them
+  double* inc;                    // [2][2]
+  const long long* step;          // device step counter
+  long long* step_next;           // where work-group 0 leaves *step + 1 after the update, or null
+  int nx;
+  R a;                            // dt / dx
+  R dt;
+  double dtd;
+  double sJx, sJy;                // fixed point -> current
+  double sEx;                     // fixed point -> Ex
+  double ay, az;                  // incident amplitude per component
+  double tr, tf, tl;              // rise, flat, fall (1/omega)
+};
+
+// Current buffers around step n: `cur` holds (push) or receives the current
+// of step n; `clear` is the one a field pass of step n zeroes.  With a fixed
+// buffer the two in use alternate: the field pass of step n clears the next
+// step's.  With three in rotation it clears the one after the next step's,
+// which neither this launch nor a push running in it touches.  Before the
+// push of step n its own buffer and, in rotation, the next one are zero.
+__device__ __forceinline__ int j_buffer(int jfix, long long n) {
+  return jfix >= 0 ? jfix : (int)((unsigned long long)n % 3ull);
+}
+__device__ __forceinline__ int j_clear(int jfix, int cur) {
+  return jfix >= 0 ? jfix ^ 1 : (cur == 0 ? 2 : cur - 1);
+}
+template <typename A>
+__device__ __forceinline__ unsigned long long* j_ptr(const A& p, int buf, int comp) {
+  return p.J + (size_t)(3 * buf + comp) * p.jstride;
+}
+
+__device__ __forceinline__ double envelope(double t, double tr, double tf, double tl) {
+  if (t <= 0.0) return 0.0;
+  if (t < tr) {
+    const double s = sin(0.5 * M_PI * t / tr);
+    return s * s;
+  }
+  t -= tr;
+  if (t < tf) return 1.0;
+  t -= tf;
+  if (t < tl) {
+    const double c = cos(0.5 * M_PI * t / tl);
+    return c * c;
+  }
+  return 0.0;
+}
+
+// Incident wave at x = 0 at t_{n+1/2} of step n, into its entry.
+template <typename R>
+__device__ __forceinline__ void incident(const FieldArgs<R>& p, long long n) {
+  const double th = ((double)n + 0.5) * p.dtd;
+  const double f = envelope(th, p.tr, p.tf, p.tl);
+  p.inc[2 * (n & 1)] = p.ay * f * sin(th);
+  p.inc[2 * (n & 1) + 1] = p.az * f * cos(th);
+}
+
+template <typename R>
+__global__ void k_incident(FieldArgs<R> p, long long n) {
+  incident<R>(p, n);
+}
+
+// The Yee update term by term, shared by the field pass and by the push
+// tiles that advance their own cells: the fused multiply-adds are written
+// out, so that both give the same bits.
+template <typename R>
+__device__ __forceinline__ R yee_bz(R bz, R ha, R ey_hi, R ey_lo) { return fma(-ha, ey_hi - ey_lo, bz); }
+template <typename R>
+__device__ __forceinline__ R yee_by(R by, R ha, R ez_hi, R ez_lo) { return fma(ha, ez_hi - ez_lo, by); }
+template <typename R>
+__device__ __forceinline__ R yee_ey(R ey, R a, R bz_hi, R bz_lo, R dt, R jy) {
+  return fma(-dt, jy, fma(-a, bz_hi - bz_lo, ey));
+}
+template <typename R>
+__device__ __forceinline__ R yee_ez(R ez, R a, R by_hi, R by_lo, R dt, R jz) {
+  return fma(-dt, jz, fma(a, by_hi - by_lo, ez));
+}
+// boundary guards at t_{n+1/2} (first-order Silver-Mueller with injection)
+template <typename R>
+__device__ __forceinline__ void guard_left(R a, R dt, R ey, R ez, R bz1, R by1, R jy, R jz, double ey_in,
+                                           double ez_in, R& bz, R& by) {
+  const R d = R(1) + a;
+  bz = (fma(dt, jy, fma(-(R(1) - a), bz1, fma(R(4), (R)ey_in, -(R(2) * ey))))) / d;
+  by = (fma(R(-4), (R)ez_in, fma(-dt, jz, fma(R(2), ez, -((R(1) - a) * by1))))) / d;
+}
+template <typename R>
+__device__ __forceinline__ void guard_right(R a, R dt, R ey, R ez, R bzn, R byn, R jy, R jz, R& bz, R& by) {
+  const R d = R(1) + a;
+  bz = (fma(-dt, jy, fma(R(2), ey, -((R(1) - a) * bzn)))) / d;
+  by = (fma(dt, jz, fma(R(-2), ez, -((R(1) - a) * byn)))) / d;
+}
+
+// LDS elements of a field chunk of CH nodes
+template <int CH>
+constexpr int field_lds_elems() { return 8 * CH + 14; }
+
+// One chunk of CH nodes (the work-group has CH threads) of step n, whose
+// current is in buffer `jb`; `sm` holds field_lds_elems<CH>() elements of LDS.
+template <typename R, int CH>
+__device__ __forceinline__ void field_chunk(const FieldArgs<R>& p, int chunk, long long n_step, int jb, R* sm) {
+  R* sEy = sm;                    // E^n, nodes i0-2 .. i0+CH
+  R* sEz = sEy + (CH + 3);
+  R* sBy = sEz + (CH + 3);        // B, half-nodes i0-1 .. i0+CH
+  R* sBz = sBy + (CH + 2);
+  R* sJy = sBz + (CH + 2);        // J, nodes i0-1 .. i0+CH-1
+  R* sJz = sJy + (CH + 1);
+  R* nEy = sJz + (CH + 1);        // E^{n+1}, nodes i0-1 .. i0+CH-1
+  R* nEz = nEy + (CH + 1);
+  const int t = threadIdx.x;
+  const int i0 = chunk * CH;
+  const int n = p.nx;
+  const R a = p.a, ha = R(0.5) * p.a, dt = p.dt;
+  const long long* J0 = (const long long*)j_ptr(p, jb, 0);
+  const long long* J1 = (const long long*)j_ptr(p, jb, 1);
+  const long long* J2 = (const long long*)j_ptr(p, jb, 2);
+
+  // loads needed only at the end are issued first, so that their latency
+  // overlaps the staged update below
+  const int h = i0 + t;  // this thread's half-node (and node) output
+  long long ex_old = 0, jx = 0;
+  if (h <= n + 1) {
+    ex_old = p.Ex_in[h];
+    jx = J0[h];
+  }
+  // incident wave at t_{n+1/2} (work-group 0 only)
+  double ey_in = 0.0, ez_in = 0.0;
+  if (t == 0 && i0 == 0) {
+    ey_in = p.inc[2 * (n_step & 1)];
+    ez_in = p.inc[2 * (n_step & 1) + 1];
+  }
+
+  for (int k = t; k < CH + 3; k += CH) {
+    const int i = i0 - 2 + k;
+    const bool ok = i >= 0 && i <= n;
+    const NodeF<R> v = ok ? p.in.N[i] : NodeF<R>{R(0), R(0)};
+    sEy[k] = v.ey;
+    sEz[k] = v.ez;
+  }
+  for (int k = t; k < CH + 2; k += CH) {
+    const int h = i0 - 1 + k;
+    const bool ok = h >= 0 && h <= n + 1;
+    const HalfF<R> v = ok ? p.in.H[h] : HalfF<R>{R(0), R(0), R(0), R(0)};
+    sBy[k] = v.by;
+    sBz[k] = v.bz;
+  }
+  for (int k = t; k < CH + 1; k += CH) {
+    const int i = i0 - 1 + k;
+    const bool ok = i >= 0 && i <= n;
+    sJy[k] = ok ? (R)((double)J1[i + 1] * p.sJy) : R(0);
+    sJz[k] = ok ? (R)((double)J2[i + 1] * p.sJy) : R(0);
+  }
+  __syncthreads();
+
+  // B^n -> B^{n+1/2} on interior half-nodes h = 1..n
+  for (int k = t; k < CH + 2; k += CH) {
+    const int h = i0 - 1 + k;
+    if (h >= 1 && h <= n) {
+      sBz[k] = yee_bz(sBz[k], ha, sEy[k + 1], sEy[k]);
+      sBy[k] = yee_by(sBy[k], ha, sEz[k + 1], sEz[k]);
+    }
+  }
+  __syncthreads();
+
+  if (t == 0 && i0 == 0)
+    // h = 0 is LDS index 1; node 0 is sEy index 2, Jy node 0 is sJy index 1
+    guard_left<R>(a, dt, sEy[2], sEz[2], sBz[2], sBy[2], sJy[1], sJz[1], ey_in, ez_in, sBz[1], sBy[1]);
+  if (t == 0 && n + 1 >= i0 && n + 1 <= i0 + CH) {
+    const int k = n + 1 - (i0 - 1);       // LDS index of h = n+1
+    const int kn = n - (i0 - 2);          // LDS index of node n in sEy
+    const int kj = n - (i0 - 1);          // LDS index of node n in sJy
+    guard_right<R>(a, dt, sEy[kn], sEz[kn], sBz[k - 1], sBy[k - 1], sJy[kj], sJz[kj], sBz[k], sBy[k]);
+  }
+  __syncthreads();
+
+  // E^n -> E^{n+1} on nodes i0-1 .. i0+CH-1
+  for (int k = t; k < CH + 1; k += CH) {
+    const int i = i0 - 1 + k;
+    if (i >= 0 && i <= n) {
+      nEy[k] = yee_ey(sEy[k + 1], a, sBz[k + 1], sBz[k], dt, sJy[k]);
+      nEz[k] = yee_ez(sEz[k + 1], a, sBy[k + 1], sBy[k], dt, sJz[k]);
+    } else {
+      nEy[k] = R(0);
+      nEz[k] = R(0);
+    }
+  }
+  __syncthreads();
+
+  // boundary bookkeeping at t_{n+1/2}
+  if (t == 0 && i0 == 0) {
+    const double eyl = 0.5 * ((double)sEy[2] + (double)nEy[1]);
+    const double ezl = 0.5 * ((double)sEz[2] + (double)nEz[1]);
+    const double bzl = 0.5 * ((double)sBz[1] + (double)sBz[2]);
+    const double byl = 0.5 * ((double)sBy[1] + (double)sBy[2]);
+    const double L1 = eyl - bzl, L2 = ezl + byl;
+    p.budget[0] += p.dtd * (ey_in * ey_in + ez_in * ez_in);
+    p.budget[1] += p.dtd * 0.25 * (L1 * L1 + L2 * L2);
+    if (p.step_next) *p.step_next = n_step + 1;
+    incident<R>(p, n_step + 1);
+  }
+  if (t == 0 && i0 <= n && n < i0 + CH) {
+    const int kn = n - (i0 - 2), ke = n - (i0 - 1), kb = n - (i0 - 1);
+    const double eyr = 0.5 * ((double)sEy[kn] + (double)nEy[ke]);
+    const double ezr = 0.5 * ((double)sEz[kn] + (double)nEz[ke]);
+    const double bzr = 0.5 * ((double)sBz[kb] + (double)sBz[kb + 1]);
+    const double byr = 0.5 * ((double)sBy[kb] + (double)sBy[kb + 1]);
+    const double R1 = eyr + bzr, R2 = ezr - byr;
+    p.budget[2] += p.dtd * 0.25 * (R1 * R1 + R2 * R2);
+  }
+
+  // own outputs: node i = i0 + t, half-node h = i0 + t
+  const int jz = j_clear(p.jfix, jb);
+  const int i = i0 + t;
+  if (i <= n) {
+    p.out.N[i] = NodeF<R>{nEy[t + 1], nEz[t + 1]};
+  }
+  if (h <= n + 1) {
+    R bz = sBz[t + 1], byv = sBy[t + 1];
+    if (h >= 1 && h <= n) {  // B^{n+1/2} -> B^{n+1} (guards keep their t_{n+1/2} value)
+      bz = yee_bz(bz, ha, nEy[t + 1], nEy[t]);
+      byv = yee_by(byv, ha, nEz[t + 1], nEz[t]);
+    }
+    const long long ex = ex_old - jx;
+    p.Ex_out[h] = ex;
+    p.out.H[h] = HalfF<R>{(R)((double)ex * p.sEx), byv, bz, R(0)};
+    j_ptr(p, jz, 0)[h] = 0ull;
+  }
+  if (i0 + t <= n + 2) {
+    j_ptr(p, jz, 1)[i0 + t] = 0ull;
+    j_ptr(p, jz, 2)[i0 + t] = 0ull;
+  }
+}
+
+template <typename R>
+__global__ __launch_bounds__(kFieldChunk) void k_field(FieldArgs<R> p) {
+  __shared__ R sm[field_lds_elems<kFieldChunk>()];
+  const long long n = *p.step;
+  field_chunk<R, kFieldChunk>(p, (int)blockIdx.x, n, j_buffer(p.jfix, n), sm);
+}
+
+// E^{n+1} at node i and (E_x, B)^{n+1} at half-node i (0 <= i <= nx + 1), by
+// one thread from E^n, B^n and the current of step n: the values field_chunk
+// writes, bit for bit.
+template <typename R>
+__device__ __forceinline__ void field_direct(const FieldArgs<R>& p, int i, long long n_step, int jb,
+                                             NodeF<R>& N1, HalfF<R>& H1) {
+  const int n = p.nx;
+  const R a = p.a, ha = R(0.5) * p.a, dt = p.dt;
+  const long long* J1 = (const long long*)j_ptr(p, jb, 1);
+  const long long* J2 = (const long long*)j_ptr(p, jb, 2);
+  // nodes i-2 .. i+1 and half-nodes i-1 .. i+1 (clamped: what lies outside
+  // enters nothing that is used)
+  NodeF<R> e[4];
+  HalfF<R> b[3];
+  R jy[2], jz[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) e[k] = ld(p.in.N, (unsigned)min(max(i - 2 + k, 0), n));
+#pragma unroll
+  for (int k = 0; k < 3; ++k) b[k] = ld(p.in.H, (unsigned)min(max(i - 1 + k, 0), n + 1));
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const unsigned m = (unsigned)min(max(i - 1 + k, 0), n) + 1u;
+    jy[k] = (R)((double)ld(J1, m) * p.sJy);
+    jz[k] = (R)((double)ld(J2, m) * p.sJy);
+  }
+  const long long ex = ld(p.Ex_in, (unsigned)i) - ld((const long long*)j_ptr(p, jb, 0), (unsigned)i);
+  R bz[3], by[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int h = i - 1 + k;
+    bz[k] = b[k].bz;
+    by[k] = b[k].by;
+    if (h >= 1 && h <= n) {
+      bz[k] = yee_bz(bz[k], ha, e[k + 1].ey, e[k].ey);
+      by[k] = yee_by(by[k], ha, e[k + 1].ez, e[k].ez);
+    }
+  }
+  if (i <= 1) {  // the guard h = 0: index 1 of i = 0, index 0 of i = 1
+    const double ey_in = p.inc[2 * (n_step & 1)], ez_in = p.inc[2 * (n_step & 1) + 1];
+    R gz, gy;
+    if (i == 0) {
+      guard_left<R>(a, dt, e[2].ey, e[2].ez, bz[2], by[2], jy[1], jz[1], ey_in, ez_in, gz, gy);
+      bz[1] = gz;
+      by[1] = gy;
+    } else {
+      guard_left<R>(a, dt, e[1].ey, e[1].ez, bz[1], by[1], jy[0], jz[0], ey_in, ez_in, gz, gy);
+      bz[0] = gz;
+      by[0] = gy;
+    }
+  }
+  if (i >= n) {  // the guard h = n + 1: index 2 of i = n, index 1 of i = n + 1
+    R gz, gy;
+    if (i == n) {
+      guard_right<R>(a, dt, e[2].ey, e[2].ez, bz[1], by[1], jy[1], jz[1], gz, gy);
+      bz[2] = gz;
+      by[2] = gy;
+    } else {
+      guard_right<R>(a, dt, e[1].ey, e[1].ez, bz[0], by[0], jy[0], jz[0], gz, gy);
+      bz[1] = gz;
+      by[1] = gy;
+    }
+  }
+  const R ey0 = yee_ey(e[1].ey, a, bz[1], bz[0], dt, jy[0]), ez0 = yee_ez(e[1].ez, a, by[1], by[0], dt, jz[0]);
+  const R ey1 = yee_ey(e[2].ey, a, bz[2], bz[1], dt, jy[1]), ez1 = yee_ez(e[2].ez, a, by[2], by[1], dt, jz[1]);
+  N1 = NodeF<R>{ey1, ez1};
+  R oz = bz[1], oy = by[1];
+  if (i >= 1 && i <= n) {
+    oz = yee_bz(oz, ha, ey1, ey0);
+    oy = yee_by(oy, ha, ez1, ez0);
+  }
+  H1 = HalfF<R>{(R)((double)ex * p.sEx), oy, oz, R(0)};
+}
+
+// The field loads of one particle's gather when its tile's fields are not
+// in LDS: computed for this particle alone.
+template <typename R>
+__device__ __forceinline__ Gath<R> gather_direct(const FieldArgs<R>& p, long long n_step, int jb,
+                                                 const PData<R>& pd) {
+  const int c = pd.c == kDead ? 0 : pd.c;
+  const int hb = pd.o + R(0.5) >= R(1);
+  Gath<R> g;
+#pragma unroll 1
+  for (int k = 0; k < 3; ++k) {
+    NodeF<R> N1;
+    HalfF<R> H1;
+    field_direct<R>(p, c + k, n_step, jb, N1, H1);
+    if (k == 0) g.n0 = N1;
+    if (k == 1) g.n1 = N1;
+    if (k == hb) g.h0 = H1;
+    if (k == hb + 1) g.h1 = H1;
+  }
+  return g;
+}
+
+// ---------------------------------------------------------------- push
 // PPT particles per thread, D of them with loads in flight (D = PPT: the
-// whole tile is loaded up front)
-template <typename R, bool RR, bool COMP, int PPT, int D>
-__device__ __forceinline__ void push_tile(const PushArgs<R>& a, int s, int tile, int n, int base,
-                                          unsigned long long* lds) {
+// whole tile is loaded up front).  FUSED: the fields at a.f are not advanced
+// yet; the tile computes those of its own cells, from *fa (the field pass of
+// the step before, n_step), into the front of its LDS, and gathers there.
+template <typename R, bool RR, bool COMP, int PPT, int D, bool FUSED>
+__device__ __forceinline__ void push_tile(const PushArgs<R>& a, int s, int tile, int base, int jw,
+                                          unsigned long long* lds, const FieldArgs<R>* fa,
+                                          long long n_step, int jr) {
   static_assert(PPT % D == 0, "the load ring must divide the tile");
   // the next particle's field loads are issued from its ring entry, which
   // must be a different entry from the current particle's
@@ -674,19 +1062,26 @@ __device__ __forceinline__ void push_tile(const PushArgs<R>& a, int s, int tile,
   __shared__ double s_red[3][kThreads / kLanes];
   const SpeciesDev<R> sp = a.sp[s];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int n = (int)a.count[s];
+  const int cap = a.cap;
+  // the tile's cell range as the previous push left it, if that is known
+  // (loaded beside the flag that says so)
+  const int known = *a.pred_in;
+  const int rlo = a.rng_in[2 * tile], rhi = a.rng_in[2 * tile + 1];
 
   // the first particles' loads overlap the window set-up below
   PData<R> ring[D];
 #pragma unroll
-  for (int k = 0; k < D; ++k) ring[k] = load_particle<R, COMP>(sp, base + k * kThreads + tid, n);
+  for (int k = 0; k < D; ++k) ring[k] = load_particle<R, COMP>(sp, base + k * kThreads + tid, n, cap);
+  if (base >= n) return;
 
   // the tile's cell range: as the previous push left it, when that is
   // known, else from a pass over the cells (from the ring when it holds the
   // whole tile)
   int cmin = INT_MAX, cmax = INT_MIN;
-  if (__builtin_amdgcn_readfirstlane(*a.pred_in)) {
-    cmin = __builtin_amdgcn_readfirstlane(a.rng_in[2 * tile]);
-    cmax = __builtin_amdgcn_readfirstlane(a.rng_in[2 * tile + 1]);
+  if (__builtin_amdgcn_readfirstlane(known)) {
+    cmin = __builtin_amdgcn_readfirstlane(rlo);
+    cmax = __builtin_amdgcn_readfirstlane(rhi);
   } else {
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
@@ -721,41 +1116,77 @@ __device__ __forceinline__ void push_tile(const PushArgs<R>& a, int s, int tile,
     return;
   }
 
+  // FUSED: fields of nodes and half-nodes cmin .. cmax + 2 into the front of
+  // the LDS, one thread per node, unless the tile is too wide to leave room
+  // for its window
+  int fslots = 0;
+  StageF<R> stage{nullptr, nullptr, 0, 0};
+  if constexpr (FUSED) {
+    constexpr int kPer = (sizeof(HalfF<R>) + sizeof(NodeF<R>)) / sizeof(unsigned long long);
+    const int len = cmax - cmin + 3;
+    if (kPer * len + 3 * (cmax - cmin + 4) <= kLdsSlots) {
+      HalfF<R>* H = reinterpret_cast<HalfF<R>*>(lds);
+      NodeF<R>* N = reinterpret_cast<NodeF<R>*>(H + len);
+      for (int e = tid; e < len; e += kThreads) {
+        NodeF<R> N1;
+        HalfF<R> H1;
+        field_direct<R>(*fa, cmin + e, n_step, jr, N1, H1);
+        H[e] = H1;
+        N[e] = N1;
+      }
+      fslots = kPer * len;
+      stage = StageF<R>{H, N, cmin, len};
+    }
+  }
+
   // window: storage indices cmin .. cmax + 3 (nodes cmin - 1 .. cmax + 2),
   // with as many private copies per slot (up to 64) as the LDS holds
   DepositCtx dc;
-  dc.lds = lds;
-  dc.J[0] = a.J[0];
-  dc.J[1] = a.J[1];
-  dc.J[2] = a.J[2];
+  dc.lds = lds + fslots;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) dc.J[k] = j_ptr(a, jw, k);
   dc.wlo = cmin;
   dc.W = cmax - cmin + 4;
   dc.qw_ref = a.qw_ref[s];
+  const int room = kLdsSlots - fslots;
   int sh = 6;
-  while (sh > 0 && 3 * dc.W * ((1 << sh) + 1) > kLdsSlots) --sh;
+  while (sh > 0 && 3 * dc.W * ((1 << sh) + 1) > room) --sh;
   dc.P = sh ? (1 << sh) + 1 : 1;
   dc.copy = lane & ((1 << sh) - 1);
   const int E = 3 * dc.W * dc.P;
-  dc.use_lds = E <= kLdsSlots;
+  dc.use_lds = E <= room;
   if (dc.use_lds)
-    for (int e = tid; e < E; e += kThreads) lds[e] = 0ull;
+    for (int e = tid; e < E; e += kThreads) dc.lds[e] = 0ull;
   __syncthreads();
 
   PushAcc acc{0.f, 0.f, 0.f, INT_MAX, INT_MIN};
   // ring slot j holds particle k0 + j; its successor D ahead is loaded
   // before particle k0 + j is computed, and the field loads of particle
   // k0 + j + 1 (whose ring entry has arrived) before those of k0 + j + D
-  Gath<R> gnext = gather_issue<R>(a.f, ring[0]);
+  auto gather = [&](const PData<R>& pd) {
+    if constexpr (FUSED) return gather_staged<R>(stage, pd);
+    else return gather_issue<R>(a.f, pd);
+  };
+  if (!FUSED || fslots) {
+    Gath<R> gnext = gather(ring[0]);
 #pragma unroll kRingUnroll
-  for (int k0 = 0; k0 < PPT; k0 += D) {
+    for (int k0 = 0; k0 < PPT; k0 += D) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const int i = base + (k0 + j) * kThreads + tid;
-      const PData<R> cur = ring[j];
-      const Gath<R> gcur = gnext;
-      if (k0 + j + 1 < PPT) gnext = gather_issue<R>(a.f, ring[(j + 1) % D]);
-      if (k0 + j + D < PPT) ring[j] = load_particle<R, COMP>(sp, i + D * kThreads, n);
-      push_particle<R, RR, COMP>(a, sp, s, i, cur, gcur, dc, acc);
+      for (int j = 0; j < D; ++j) {
+        const int i = base + (k0 + j) * kThreads + tid;
+        const PData<R> cur = ring[j];
+        const Gath<R> gcur = gnext;
+        if (k0 + j + 1 < PPT) gnext = gather(ring[(j + 1) % D]);
+        if (k0 + j + D < PPT) ring[j] = load_particle<R, COMP>(sp, i + D * kThreads, n, cap);
+        push_particle<R, RR, COMP>(a, sp, s, i, cur, gcur, dc, acc);
+      }
+    }
+  } else if constexpr (FUSED) {  // a tile wider than the LDS: rare, one particle after the other
+#pragma unroll 1
+    for (int k = 0; k < PPT; ++k) {
+      const int i = base + k * kThreads + tid;
+      const PData<R> cur = load_particle<R, COMP>(sp, i, n, cap);
+      push_particle<R, RR, COMP>(a, sp, s, i, cur, gather_direct<R>(*fa, n_step, jr, cur), dc, acc);
     }
   }
 
@@ -781,13 +1212,13 @@ __device__ __forceinline__ void push_tile(const PushArgs<R>& a, int s, int tile,
       const int sl = s0 + gi;
       long long v = 0;
       if (sl < S) {
-        const unsigned long long* q = lds + sl * dc.P + t;
+        const unsigned long long* q = dc.lds + sl * dc.P + t;
         for (int k = 0; k < nc; k += g) v += (long long)q[k];
       }
       v = group_sum(v, g);
       if (t == g - 1 && sl < S && v != 0) {
         const int comp = sl / dc.W, j = sl - comp * dc.W;
-        atomicAdd(a.J[comp] + dc.wlo + j, (unsigned long long)(v * (long long)dc.qw_ref));
+        atomicAdd(j_ptr(a, jw, comp) + dc.wlo + j, (unsigned long long)(v * (long long)dc.qw_ref));
       }
     }
   }
@@ -811,21 +1242,22 @@ __device__ __forceinline__ void push_tile(const PushArgs<R>& a, int s, int tile,
   }
 }
 
-template <typename R, int PPT, int D>
-__device__ __forceinline__ void push_one_tile(const PushArgs<R>& a, int tile,
-                                              unsigned long long* lds) {
+// Tile `tile` of a push whose current goes to buffer jw.  FUSED: with the
+// field pass *fa of step n_step, whose current is in buffer jr, still due.
+template <typename R, int PPT, int D, bool FUSED = false>
+__device__ __forceinline__ void push_one_tile(const PushArgs<R>& a, int tile, int jw, unsigned long long* lds,
+                                              const FieldArgs<R>* fa = nullptr, long long n_step = 0,
+                                              int jr = 0) {
   const int s = tile < a.tiles0 ? 0 : 1;
   const int tl = s ? tile - a.tiles0 : tile;
-  const int n = (int)a.count[s];
   const int base = tl * (kThreads * PPT);
-  if (base >= n) return;
   if (s == 0 && a.rr0) {
     if (a.comp)
-      push_tile<R, true, true, PPT, D>(a, s, tile, n, base, lds);
+      push_tile<R, true, true, PPT, D, FUSED>(a, s, tile, base, jw, lds, fa, n_step, jr);
     else
-      push_tile<R, true, false, PPT, D>(a, s, tile, n, base, lds);
+      push_tile<R, true, false, PPT, D, FUSED>(a, s, tile, base, jw, lds, fa, n_step, jr);
   } else {
-    push_tile<R, false, false, PPT, D>(a, s, tile, n, base, lds);
+    push_tile<R, false, false, PPT, D, FUSED>(a, s, tile, base, jw, lds, fa, n_step, jr);
   }
 }
 
@@ -837,207 +1269,52 @@ __device__ __forceinline__ void push_one_tile(const PushArgs<R>& a, int tile,
 
 // one work-group per tile
 template <typename R>
-__global__ PIC_PUSH_BOUNDS void k_push(PushArgs<R> a) {
-  __shared__ unsigned long long lds[kLdsSlots];
-  push_one_tile<R, kPPT, kDepth>(a, a.tile0 + (int)blockIdx.x, lds);
+__global__ PIC_PUSH_BOUNDS void k_push(PushArgs<R>) {
+  const PushArgs<R>& a = kernel_args<PushArgs<R>>();
+  __shared__ __align__(16) unsigned long long lds[kLdsSlots];
+  const int jw = j_buffer(a.jfix, a.jfix >= 0 ? 0 : *a.step);
+  push_one_tile<R, kPPT, kDepth>(a, a.tile0 + (int)blockIdx.x, jw, lds);
 }
 
 // the same push in tiles of kBatchTile (two particles' loads in flight, as
 // in the batched push), for runs too small to fill the device with kTile tiles
 template <typename R>
-__global__ PIC_PUSH_BOUNDS void k_push_small(PushArgs<R> a) {
-  __shared__ unsigned long long lds[kLdsSlots];
-  push_one_tile<R, kBatchPPT, kBatchDepth>(a, a.tile0 + (int)blockIdx.x, lds);
+__global__ PIC_PUSH_BOUNDS void k_push_small(PushArgs<R>) {
+  const PushArgs<R>& a = kernel_args<PushArgs<R>>();
+  __shared__ __align__(16) unsigned long long lds[kLdsSlots];
+  const int jw = j_buffer(a.jfix, a.jfix >= 0 ? 0 : *a.step);
+  push_one_tile<R, kBatchPPT, kBatchDepth>(a, a.tile0 + (int)blockIdx.x, jw, lds);
 }
 
-// ---------------------------------------------------------------- fields
+// One launch per step for small runs: the field pass of step n (f) and the
+// push of step n + 1 (a) together.  Both read only E^n, B^n and the current
+// of step n: every push tile advances the fields of its own cells into LDS,
+// by the arithmetic of the field pass, while the work-groups after the push
+// tiles advance the whole grid for the next launch and the diagnostics.  The
+// push deposits into the next current buffer of three, and the field pass
+// clears the third.  A step of a small run is bound by the latency of its
+// launches, not by the few MB it moves: 12,800 particles in FP32 took 8.9 us
+// (push) + 4.5 us (fields) and a gap per step, now 9.3 us; 4e5 in FP64
+// 12.7 + 4.9, now 12.8 us.
 template <typename R>
-struct FieldArgs {
-  FieldsDev<R> in, out;           // E^n, B^n -> E^{n+1}, B^{n+1}
-  const long long* J[3];          // current of this step
-  unsigned long long* Jnext[3];   // current buffer of the next step, zeroed here
-  long long* Ex_int;
-  double* budget;                 // [0] E_in, [1] E_out_left, [2] E_out_right
-  long long* step;                // device step counter
-  int tick;                       // 1: work-group 0 advances *step after the update
-  int nx;
-  R a;                            // dt / dx
-  R dt;
-  double dtd;
-  double sJx, sJy;                // fixed point -> current
-  double sEx;                     // fixed point -> Ex
-  double ay, az;                  // incident amplitude per component
-  double tr, tf, tl;              // rise, flat, fall (1/omega)
+struct StepArgs {
+  PushArgs<R> a;
+  FieldArgs<R> f;
 };
 
-__device__ __forceinline__ double envelope(double t, double tr, double tf, double tl) {
-  if (t <= 0.0) return 0.0;
-  if (t < tr) {
-    const double s = sin(0.5 * M_PI * t / tr);
-    return s * s;
-  }
-  t -= tr;
-  if (t < tf) return 1.0;
-  t -= tf;
-  if (t < tl) {
-    const double c = cos(0.5 * M_PI * t / tl);
-    return c * c;
-  }
-  return 0.0;
-}
-
-// LDS elements of a field chunk of CH nodes
-template <int CH>
-constexpr int field_lds_elems() { return 8 * CH + 14; }
-
-// One chunk of CH nodes (the work-group has CH threads).  `ahead` is the
-// number of steps the run is past its device step counter (a launch that
-// advances several steps before the counter moves); `sm` holds
-// field_lds_elems<CH>() elements of LDS.
-template <typename R, int CH>
-__device__ __forceinline__ void field_chunk(const FieldArgs<R>& p, int chunk, int ahead, R* sm) {
-  R* sEy = sm;                    // E^n, nodes i0-2 .. i0+CH
-  R* sEz = sEy + (CH + 3);
-  R* sBy = sEz + (CH + 3);        // B, half-nodes i0-1 .. i0+CH
-  R* sBz = sBy + (CH + 2);
-  R* sJy = sBz + (CH + 2);        // J, nodes i0-1 .. i0+CH-1
-  R* sJz = sJy + (CH + 1);
-  R* nEy = sJz + (CH + 1);        // E^{n+1}, nodes i0-1 .. i0+CH-1
-  R* nEz = nEy + (CH + 1);
-  const int t = threadIdx.x;
-  const int i0 = chunk * CH;
-  const int n = p.nx;
-  const R a = p.a, ha = R(0.5) * p.a, dt = p.dt;
-
-  // loads needed only at the end are issued first, so that their latency
-  // overlaps the staged update below
-  const int h = i0 + t;  // this thread's half-node (and node) output
-  long long ex_old = 0, jx = 0;
-  if (h <= n + 1) {
-    ex_old = p.Ex_int[h];
-    jx = p.J[0][h];
-  }
-  // incident wave at t_{n+1/2} (work-group 0 only)
-  double ey_in = 0.0, ez_in = 0.0;
-  if (t == 0 && i0 == 0) {
-    const double th = ((double)(*p.step + ahead) + 0.5) * p.dtd;
-    const double f = envelope(th, p.tr, p.tf, p.tl);
-    ey_in = p.ay * f * sin(th);
-    ez_in = p.az * f * cos(th);
-  }
-
-  for (int k = t; k < CH + 3; k += CH) {
-    const int i = i0 - 2 + k;
-    const bool ok = i >= 0 && i <= n;
-    const NodeF<R> v = ok ? p.in.N[i] : NodeF<R>{R(0), R(0)};
-    sEy[k] = v.ey;
-    sEz[k] = v.ez;
-  }
-  for (int k = t; k < CH + 2; k += CH) {
-    const int h = i0 - 1 + k;
-    const bool ok = h >= 0 && h <= n + 1;
-    const HalfF<R> v = ok ? p.in.H[h] : HalfF<R>{R(0), R(0), R(0), R(0)};
-    sBy[k] = v.by;
-    sBz[k] = v.bz;
-  }
-  for (int k = t; k < CH + 1; k += CH) {
-    const int i = i0 - 1 + k;
-    const bool ok = i >= 0 && i <= n;
-    sJy[k] = ok ? (R)((double)p.J[1][i + 1] * p.sJy) : R(0);
-    sJz[k] = ok ? (R)((double)p.J[2][i + 1] * p.sJy) : R(0);
-  }
-  __syncthreads();
-
-  // B^n -> B^{n+1/2} on interior half-nodes h = 1..n
-  for (int k = t; k < CH + 2; k += CH) {
-    const int h = i0 - 1 + k;
-    if (h >= 1 && h <= n) {
-      sBz[k] -= ha * (sEy[k + 1] - sEy[k]);
-      sBy[k] += ha * (sEz[k + 1] - sEz[k]);
-    }
-  }
-  __syncthreads();
-
-  // boundary guards at t_{n+1/2} (first-order Silver-Mueller with injection)
-  if (t == 0 && i0 == 0) {
-    // h = 0 is LDS index 1; node 0 is sEy index 2, Jy node 0 is sJy index 1
-    const R d = R(1) + a;
-    sBz[1] = (R(4) * (R)ey_in - R(2) * sEy[2] - (R(1) - a) * sBz[2] + dt * sJy[1]) / d;
-    sBy[1] = (R(2) * sEz[2] - (R(1) - a) * sBy[2] - dt * sJz[1] - R(4) * (R)ez_in) / d;
-  }
-  if (t == 0 && n + 1 >= i0 && n + 1 <= i0 + CH) {
-    const int k = n + 1 - (i0 - 1);       // LDS index of h = n+1
-    const int kn = n - (i0 - 2);          // LDS index of node n in sEy
-    const int kj = n - (i0 - 1);          // LDS index of node n in sJy
-    const R d = R(1) + a;
-    sBz[k] = (R(2) * sEy[kn] - (R(1) - a) * sBz[k - 1] - dt * sJy[kj]) / d;
-    sBy[k] = (R(-2) * sEz[kn] - (R(1) - a) * sBy[k - 1] + dt * sJz[kj]) / d;
-  }
-  __syncthreads();
-
-  // E^n -> E^{n+1} on nodes i0-1 .. i0+CH-1
-  for (int k = t; k < CH + 1; k += CH) {
-    const int i = i0 - 1 + k;
-    if (i >= 0 && i <= n) {
-      nEy[k] = sEy[k + 1] - a * (sBz[k + 1] - sBz[k]) - dt * sJy[k];
-      nEz[k] = sEz[k + 1] + a * (sBy[k + 1] - sBy[k]) - dt * sJz[k];
-    } else {
-      nEy[k] = R(0);
-      nEz[k] = R(0);
-    }
-  }
-  __syncthreads();
-
-  // boundary bookkeeping at t_{n+1/2}
-  if (t == 0 && i0 == 0) {
-    const double eyl = 0.5 * ((double)sEy[2] + (double)nEy[1]);
-    const double ezl = 0.5 * ((double)sEz[2] + (double)nEz[1]);
-    const double bzl = 0.5 * ((double)sBz[1] + (double)sBz[2]);
-    const double byl = 0.5 * ((double)sBy[1] + (double)sBy[2]);
-    const double L1 = eyl - bzl, L2 = ezl + byl;
-    p.budget[0] += p.dtd * (ey_in * ey_in + ez_in * ez_in);
-    p.budget[1] += p.dtd * 0.25 * (L1 * L1 + L2 * L2);
-    if (p.tick) *p.step += 1;
-  }
-  if (t == 0 && i0 <= n && n < i0 + CH) {
-    const int kn = n - (i0 - 2), ke = n - (i0 - 1), kb = n - (i0 - 1);
-    const double eyr = 0.5 * ((double)sEy[kn] + (double)nEy[ke]);
-    const double ezr = 0.5 * ((double)sEz[kn] + (double)nEz[ke]);
-    const double bzr = 0.5 * ((double)sBz[kb] + (double)sBz[kb + 1]);
-    const double byr = 0.5 * ((double)sBy[kb] + (double)sBy[kb + 1]);
-    const double R1 = eyr + bzr, R2 = ezr - byr;
-    p.budget[2] += p.dtd * 0.25 * (R1 * R1 + R2 * R2);
-  }
-
-  // own outputs: node i = i0 + t, half-node h = i0 + t
-  const int i = i0 + t;
-  if (i <= n) {
-    p.out.N[i] = NodeF<R>{nEy[t + 1], nEz[t + 1]};
-  }
-  if (h <= n + 1) {
-    R bz, byv;
-    if (h >= 1 && h <= n) {  // B^{n+1/2} -> B^{n+1}
-      bz = sBz[t + 1] - ha * (nEy[t + 1] - nEy[t]);
-      byv = sBy[t + 1] + ha * (nEz[t + 1] - nEz[t]);
-    } else {                 // guards keep their t_{n+1/2} value
-      bz = sBz[t + 1];
-      byv = sBy[t + 1];
-    }
-    const long long ex = ex_old - jx;
-    p.Ex_int[h] = ex;
-    p.out.H[h] = HalfF<R>{(R)((double)ex * p.sEx), byv, bz, R(0)};
-    p.Jnext[0][h] = 0ull;
-  }
-  if (i0 + t <= n + 2) {
-    p.Jnext[1][i0 + t] = 0ull;
-    p.Jnext[2][i0 + t] = 0ull;
-  }
-}
-
 template <typename R>
-__global__ __launch_bounds__(kFieldChunk) void k_field(FieldArgs<R> p) {
-  __shared__ R sm[field_lds_elems<kFieldChunk>()];
-  field_chunk<R, kFieldChunk>(p, (int)blockIdx.x, 0, sm);
+__global__ PIC_PUSH_BOUNDS void k_step(StepArgs<R>) {
+  const PushArgs<R>& a = kernel_args<StepArgs<R>>().a;
+  const FieldArgs<R>& f = kernel_args<StepArgs<R>>().f;
+  __shared__ __align__(16) unsigned long long lds[kLdsSlots];
+  static_assert(field_lds_elems<kThreads>() * sizeof(R) <= sizeof(lds), "field chunk must fit the window");
+  const long long n = *f.step;
+  const int jr = j_buffer(-1, n), jw = jr == 2 ? 0 : jr + 1;
+  const int b = (int)blockIdx.x;
+  if (b < a.ntiles)
+    push_one_tile<R, kBatchPPT, kBatchDepth, true>(a, b, jw, lds, &f, n, jr);
+  else
+    field_chunk<R, kThreads>(f, b - a.ntiles, n, jr, reinterpret_cast<R*>(lds));
 }
 
 // ---------------------------------------------------------------- sort
@@ -1485,7 +1762,7 @@ __global__ void k_check_rounding(unsigned first, unsigned count, unsigned long l
 template <typename R>
 struct SlotDev {
   PushArgs<R> push[2][2];   // [particle parity][field parity]
-  FieldArgs<R> field[2];    // [field parity]; tick = 0 (the field pass advances the counter itself)
+  FieldArgs<R> field[2];    // [field parity] (the quantum's last field pass advances the counter itself)
   SortArgs<R> sort[2];      // [source particle parity]
   int* cnt[2];
   int* cur[2];
@@ -1542,39 +1819,79 @@ __device__ __forceinline__ SlotRanges load_ranges(const int* start, int n, int* 
 // grid-stride loop here would keep more values live and cost occupancy).
 template <typename R>
 __global__ PIC_PUSH_BOUNDS void k_push_batch(const SlotDev<R>* __restrict__ slots, const int* __restrict__ start, int n) {
-  __shared__ unsigned long long lds[kLdsSlots];
+  __shared__ __align__(16) unsigned long long lds[kLdsSlots];
   // the slot table and the deposit window share the LDS: every wave reads
   // the table before the barrier below, the window is cleared after it
-  static_assert((kMaxSlots + 1) * sizeof(int) <= sizeof(lds), "slot ranges must fit the window");
+  static_assert(2 * (kMaxSlots + 1) * sizeof(int) <= sizeof(lds), "slot ranges must fit the window");
   const SlotRanges sr = load_ranges(start, n, reinterpret_cast<int*>(lds));
   const int b = (int)blockIdx.x;
   if (b >= sr.total()) return;  // block-uniform, as are the returns below
   const int sl = sr.slot(b);
   const int tile = b - sr.first(sl);
   __syncthreads();
-  const SlotDev<R>& S = slots[sl];
+  const SlotDev<R>& S = constant_ref(slots + sl);
   const long long st = uniform(*S.step);
   if (st >= S.target) return;
   const int pp = (int)((st / S.sort_interval) & 1), fp = (int)(st & 1);
-  push_one_tile<R, kBatchPPT, kBatchDepth>(S.push[pp][fp], tile, lds);
+  push_one_tile<R, kBatchPPT, kBatchDepth>(S.push[pp][fp], tile, j_buffer(-1, st), lds);
 }
 
-// The field pass also ends the step: the last of a run's chunks to finish
-// advances the run's step counter (every chunk of the run has read the
-// counter before it counts itself done).
+// k_step for every resident run: step q >= 1 of the quantum is pushed after
+// step q - 1's fields (24 requests in three groups: 26 us, where the push and
+// the field launch took 24.3 + 7.7 us).  The step counters stay put during the quantum (every
+// launch computes its step as counter + q) and advance at its end.
+template <typename R>
+__global__ PIC_PUSH_BOUNDS void k_step_batch(const SlotDev<R>* __restrict__ slots,
+                                             const int* __restrict__ push_start,
+                                             const int* __restrict__ field_start, int n, int q) {
+  __shared__ __align__(16) unsigned long long lds[kLdsSlots];
+  int* rp = reinterpret_cast<int*>(lds);
+  int* rf = rp + n + 1;
+  for (int i = threadIdx.x; i <= n; i += kThreads) {
+    rp[i] = push_start[i];
+    rf[i] = field_start[i];
+  }
+  __syncthreads();
+  const SlotRanges P{rp, n}, F{rf, n};
+  int b = (int)blockIdx.x;
+  const bool push = b < P.total();
+  if (!push) b -= P.total();
+  const SlotRanges& sr = push ? P : F;
+  if (b >= sr.total()) return;
+  const int sl = sr.slot(b);
+  const int item = b - sr.first(sl);
+  __syncthreads();  // the tables are read: the LDS is free
+  const SlotDev<R>& S = constant_ref(slots + sl);
+  const long long st = uniform(*S.step) + q - 1;  // the step whose fields are due
+  if (st >= S.target) return;
+  const int jr = j_buffer(-1, st);
+  if (push) {
+    if (st + 1 >= S.target) return;
+    const int pp = (int)(((st + 1) / S.sort_interval) & 1), fp = (int)((st + 1) & 1);
+    push_one_tile<R, kBatchPPT, kBatchDepth, true>(S.push[pp][fp], item, jr == 2 ? 0 : jr + 1, lds,
+                                                   &S.field[st & 1], st, jr);
+  } else {
+    field_chunk<R, kThreads>(S.field[st & 1], item, st, jr, reinterpret_cast<R*>(lds));
+  }
+}
+
+// The last field pass of a quantum of q steps also ends it: the last of a
+// run's chunks to finish advances the run's step counter (every chunk of the
+// run has read the counter before it counts itself done).
 template <typename R>
 __global__ __launch_bounds__(kFieldChunk) void k_field_batch(const SlotDev<R>* __restrict__ slots,
-                                                            const int* __restrict__ start, int n) {
+                                                            const int* __restrict__ start, int n, int q) {
   __shared__ int rng[kMaxSlots + 1];
   __shared__ R sm[field_lds_elems<kFieldChunk>()];
   const SlotRanges sr = load_ranges(start, n, rng);
   const int b = (int)blockIdx.x;
   if (b >= sr.total()) return;
   const int sl = sr.slot(b);
-  const SlotDev<R>& S = slots[sl];
-  const long long st = uniform(*S.step);
-  if (st >= S.target) return;
-  field_chunk<R, kFieldChunk>(S.field[st & 1], b - sr.first(sl), 0, sm);
+  const SlotDev<R>& S = constant_ref(slots + sl);
+  const long long s0 = uniform(*S.step), st = s0 + q - 1;
+  if (s0 >= S.target) return;
+  if (st < S.target)  // (a run that ends inside the quantum had its last fields advanced before)
+    field_chunk<R, kFieldChunk>(S.field[st & 1], b - sr.first(sl), st, j_buffer(-1, st), sm);
   // relaxed: a block's read of the counter has returned (its value chose the
   // buffers) before the block counts itself; acquire/release ordering here
   // would write back and invalidate the L2 once per work-group
@@ -1582,7 +1899,7 @@ __global__ __launch_bounds__(kFieldChunk) void k_field_batch(const SlotDev<R>* _
     const int chunks = sr.first(sl + 1) - sr.first(sl);
     if (__hip_atomic_fetch_add(S.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == chunks - 1) {
       __hip_atomic_store(S.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      *S.step = st + 1;
+      *S.step = s0 + q < S.target ? s0 + q : S.target;
     }
   }
 }
@@ -1612,7 +1929,7 @@ template <typename R>
 __global__ __launch_bounds__(1024) void k_sort_scan_batch(const SlotDev<R>* slots, int n) {
   for (int w = (int)blockIdx.x; w < 2 * n; w += (int)gridDim.x) {
     const int sl = w >> 1, sp = w & 1;
-    const SlotDev<R>& S = slots[sl];
+    const SlotDev<R>& S = constant_ref(slots + sl);
     int q;
     if (!sort_due(S, &q)) continue;
     __syncthreads();
@@ -1705,7 +2022,7 @@ __global__ __launch_bounds__(kThreads, PIC_STEPS_MIN_WAVES) void k_steps_batch(c
                                               const int* __restrict__ push_start,
                                               const int* __restrict__ field_start, int n, int steps,
                                               unsigned* bar, int* err, unsigned long long ticks) {
-  __shared__ unsigned long long lds[kLdsSlots];
+  __shared__ __align__(16) unsigned long long lds[kLdsSlots];
   __shared__ int rp[kPersistSlots + 1], rf[kPersistSlots + 1];
   static_assert(field_lds_elems<kThreads>() * sizeof(double) <= sizeof(lds), "field chunk must fit the window");
   for (int i = threadIdx.x; i <= n; i += blockDim.x) {
@@ -1718,21 +2035,21 @@ __global__ __launch_bounds__(kThreads, PIC_STEPS_MIN_WAVES) void k_steps_batch(c
   for (int k = 0; k < steps; ++k) {
     for (int b = (int)blockIdx.x; b < P.total(); b += G) {
       const int sl = P.slot(b);
-      const SlotDev<R>& S = slots[sl];
+      const SlotDev<R>& S = constant_ref(slots + sl);
       const long long st = uniform(*S.step) + k;
       if (st >= S.target) continue;
       const int pp = (int)((st / S.sort_interval) & 1), fp = (int)(st & 1);
       __syncthreads();  // the block's previous tile is out of the window
-      push_one_tile<R, kBatchPPT, kBatchDepth>(S.push[pp][fp], b - P.first(sl), lds);
+      push_one_tile<R, kBatchPPT, kBatchDepth>(S.push[pp][fp], b - P.first(sl), j_buffer(-1, st), lds);
     }
     grid_sync(bar, err, ticks);
     for (int b = (int)blockIdx.x; b < F.total(); b += G) {
       const int sl = F.slot(b);
-      const SlotDev<R>& S = slots[sl];
+      const SlotDev<R>& S = constant_ref(slots + sl);
       const long long st = uniform(*S.step) + k;
       if (st >= S.target) continue;
       __syncthreads();
-      field_chunk<R, kThreads>(S.field[st & 1], b - F.first(sl), k, reinterpret_cast<R*>(lds));
+      field_chunk<R, kThreads>(S.field[st & 1], b - F.first(sl), st, j_buffer(-1, st), reinterpret_cast<R*>(lds));
     }
     grid_sync(bar, err, ticks);
   }

@@ -139,15 +139,21 @@ struct pic_run {
   SpeciesBuf sp[2][2];  // [species][parity]
   void* FN[2];          // [parity] node fields (E_y, E_z)
   void* FH[2];          // [parity] half-node fields (E_x, B_y, B_z, 0)
-  unsigned long long* J[2][3];
-  long long* Ex_int;
+  // Currents: three buffers of (Jx, Jy, Jz), jstride apart.  Runs pushed in
+  // small tiles, and every run inside a batch, rotate through them (step mod
+  // 3), which lets one launch advance the fields of a step and push the next;
+  // other runs alternate between the first two (step mod 2).
+  unsigned long long* J;
+  size_t jstride;
+  long long* Ex_int[2]; // [step parity]
   long long* count;     // [parity][species]
-  long long* step_dev;
+  long long* step_dev;  // [step parity] device step counter (a batch keeps it in entry 0)
   int* flags;
   double* acc;          // [tiles][4]
   int* trange;          // [2 parities][tiles][2]: tile cell ranges left by the push
   int* tpred;           // [2 parities]: the ranges of that parity match the particles
   double* budget;       // [4]
+  double* inc;          // [2][2] incident wave by step parity
   int* cnt[2];
   int* cursor[2];
   long long* rho;
@@ -204,17 +210,18 @@ void carve(pic_run* r, Carver& cv) {
     r->FN[p] = cv.take<char>((size_t)(d.nx + 1) * 2 * rs);
     r->FH[p] = cv.take<char>((size_t)(d.nx + 2) * 4 * rs);
   }
-  for (int p = 0; p < 2; ++p)
-    for (int k = 0; k < 3; ++k) r->J[p][k] = cv.take<unsigned long long>(d.nx + 3);
-  r->Ex_int = cv.take<long long>(d.nx + 2);
+  r->jstride = ((size_t)d.nx + 3 + 31) & ~size_t(31);  // 256-byte aligned components
+  r->J = cv.take<unsigned long long>(9 * r->jstride);
+  for (int p = 0; p < 2; ++p) r->Ex_int[p] = cv.take<long long>(d.nx + 2);
   r->count = cv.take<long long>(4);
-  r->step_dev = cv.take<long long>(1);
+  r->step_dev = cv.take<long long>(2);
   r->flags = cv.take<int>(4);
   r->tiles_max = 2 * tiles_for(d.cap, kMinTile);  // a run may also step in a batch
   r->acc = cv.take<double>(4 * (size_t)std::max(r->tiles_max, 1));
   r->trange = cv.take<int>(4 * (size_t)std::max(r->tiles_max, 1));
   r->tpred = cv.take<int>(2);
   r->budget = cv.take<double>(4);
+  r->inc = cv.take<double>(4);
   for (int s = 0; s < 2; ++s) {
     r->cnt[s] = cv.take<int>(d.nx + 1);
     r->cursor[s] = cv.take<int>(d.nx + 1);
@@ -303,6 +310,17 @@ int sort_blocks_for(long long n) {
   return (int)std::max<long long>(1, (n + kSortTile - 1) / kSortTile);
 }
 
+// Runs in small tiles advance a step's fields and push the next in one
+// launch: their step is bound by launch latency.  The large tiles' push is
+// bound by HBM and keeps its own launch.
+bool fused_steps(const pic_run* r) { return r->push_tile != kTile; }
+
+// Current buffer of run r's step n (outside a batch).
+int j_index(const pic_run* r, long long n) { return (int)(fused_steps(r) ? n % 3 : n & 1); }
+unsigned long long* j_buf(const pic_run* r, int buf, int comp) {
+  return r->J + (3 * (size_t)buf + comp) * r->jstride;
+}
+
 // Kernel arguments of run r for particle buffer parity pp and field parity fp.
 template <typename R>
 PushArgs<R> make_push_args(const pic_run* r, int pp, int fp, int tile = kTile) {
@@ -312,7 +330,11 @@ PushArgs<R> make_push_args(const pic_run* r, int pp, int fp, int tile = kTile) {
   a.count = r->count + 2 * pp;
   a.tiles0 = tiles_for(r->n_max[0], tile);
   a.f = fdev<R>(r, fp);
-  for (int k = 0; k < 3; ++k) a.J[k] = r->J[fp][k];
+  a.J = r->J;
+  a.jstride = (unsigned)r->jstride;
+  a.jfix = fused_steps(r) ? -1 : fp;
+  a.step = r->step_dev + fp;
+  a.cap = (int)d.cap;
   a.acc = r->acc;
   a.flags = r->flags;
   a.nx = d.nx;
@@ -339,20 +361,23 @@ PushArgs<R> make_push_args(const pic_run* r, int pp, int fp, int tile = kTile) {
   return a;
 }
 
+// Field pass of step parity p; `batch`: as a slot of a batch (one step
+// counter, currents in rotation, the counter advanced by the batch's pass).
 template <typename R>
-FieldArgs<R> make_field_args(const pic_run* r, int p, int tick) {
+FieldArgs<R> make_field_args(const pic_run* r, int p, bool batch) {
   const Derived& d = r->d;
   FieldArgs<R> f{};
   f.in = fdev<R>(r, p);
   f.out = fdev<R>(r, p ^ 1);
-  for (int k = 0; k < 3; ++k) {
-    f.J[k] = (const long long*)r->J[p][k];
-    f.Jnext[k] = r->J[p ^ 1][k];
-  }
-  f.Ex_int = r->Ex_int;
+  f.J = r->J;
+  f.jstride = (unsigned)r->jstride;
+  f.jfix = batch || fused_steps(r) ? -1 : p;
+  f.Ex_in = r->Ex_int[p];
+  f.Ex_out = r->Ex_int[p ^ 1];
   f.budget = r->budget;
-  f.step = r->step_dev;
-  f.tick = tick;
+  f.inc = r->inc;
+  f.step = batch ? r->step_dev : r->step_dev + p;
+  f.step_next = batch ? nullptr : r->step_dev + (p ^ 1);
   f.nx = d.nx;
   f.a = (R)r->cfg.cfl;
   f.dt = (R)d.dt;
@@ -429,7 +454,7 @@ pic_status launch_push(pic_run* r, hipStream_t st, bool capture = false) {
 
 template <typename R>
 pic_status launch_field(pic_run* r, hipStream_t st, bool capture = false) {
-  const FieldArgs<R> f = make_field_args<R>(r, (int)(r->step & 1), 1);
+  const FieldArgs<R> f = make_field_args<R>(r, (int)(r->step & 1), false);
   if (capture) {
     hipLaunchKernelGGL(k_field<R>, dim3(field_blocks_for(r)), dim3(kFieldChunk), 0, st, f);
   } else {
@@ -481,6 +506,32 @@ pic_status launch_sort(pic_run* r, hipStream_t st, bool capture = false) {
   return PIC_OK;
 }
 
+// The field pass of the current step and the push of the next, one launch.
+template <typename R>
+pic_status launch_step(pic_run* r, hipStream_t st) {
+  const int p = (int)(r->step & 1);
+  const StepArgs<R> s{make_push_args<R>(r, r->pp, p ^ 1, r->push_tile), make_field_args<R>(r, p, false)};
+  const int chunks = (r->d.nx + 3 + kThreads - 1) / kThreads;
+  hipLaunchKernelGGL(k_step<R>, dim3(s.a.ntiles + chunks), dim3(kThreads), 0, st, s);
+  HIP_TRY(hipGetLastError());
+  r->step += 1;
+  return PIC_OK;
+}
+
+// n >= 1 steps of a run in small tiles: a push, n - 1 launches that advance
+// the fields and push again, and the last field pass; the sorts due fall
+// before the pushes (they do not touch the grid).
+template <typename R>
+pic_status run_steps(pic_run* r, int64_t n, hipStream_t st, bool capture) {
+  pic_status ps;
+  for (int64_t k = 0; k < n; ++k) {
+    const long long s = r->step + (k > 0);  // the step to push
+    if (s > 0 && s % r->cfg.sort_interval == 0 && (ps = launch_sort<R>(r, st, capture))) return ps;
+    if ((ps = k ? launch_step<R>(r, st) : launch_push<R>(r, st, capture))) return ps;
+  }
+  return launch_field<R>(r, st, capture);
+}
+
 template <typename R>
 pic_status one_step(pic_run* r, hipStream_t st, bool capture = false) {
   if (r->step > 0 && r->step % r->cfg.sort_interval == 0) {
@@ -515,7 +566,10 @@ pic_status capture_steps(pic_run* r, int64_t span) {
   const int pp = r->pp, fp = (int)(r->step & 1);
   HIP_TRY(hipStreamBeginCapture(r->capture_stream, hipStreamCaptureModeThreadLocal));
   pic_status ps = PIC_OK;
-  for (int64_t k = 0; k < span && !ps; ++k) ps = one_step<R>(r, r->capture_stream, true);
+  if (fused_steps(r) && !r->max_grid)
+    ps = run_steps<R>(r, span, r->capture_stream, true);
+  else
+    for (int64_t k = 0; k < span && !ps; ++k) ps = one_step<R>(r, r->capture_stream, true);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(r->capture_stream, &g);
   if (ps) {
@@ -553,9 +607,19 @@ pic_status do_steps(pic_run* r, int64_t n, hipStream_t st) {
       }
       continue;
     }
-    pic_status ps = one_step<R>(r, st);
+    // up to the next sort step, where a graph may start (all that is left,
+    // if none can)
+    int64_t m = 1;
+    pic_status ps;
+    if (fused_steps(r) && !r->timing && !r->max_grid) {
+      const int64_t K = r->cfg.sort_interval, to_sort = K - r->step % K;
+      m = n - to_sort >= span && span <= kMaxGraphSteps ? to_sort : n;
+      ps = run_steps<R>(r, m, st, false);
+    } else {
+      ps = one_step<R>(r, st);
+    }
     if (ps) return ps;
-    --n;
+    n -= m;
   }
   return PIC_OK;
 }
@@ -571,6 +635,7 @@ pic_status do_init(pic_run* r, hipStream_t st) {
                        (unsigned long long)r->cfg.seed, r->cfg.jitter, (R)d.w_ref);
   }
   hipLaunchKernelGGL(k_set_counts, dim3(1), dim3(1), 0, st, r->count, n, n);
+  hipLaunchKernelGGL(k_incident<R>, dim3(1), dim3(1), 0, st, make_field_args<R>(r, 0, false), 0ll);
   HIP_TRY(hipGetLastError());
   return PIC_OK;
 }
@@ -590,7 +655,7 @@ pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   for (int s = 0; s < 2; ++s) p.sp[s] = dev<R>(r->sp[s][r->pp]);
   p.count = r->count + 2 * r->pp;
   p.f = fdev<R>(r, (int)(r->step & 1));
-  p.Ex_int = r->Ex_int;
+  p.Ex_int = r->Ex_int[r->step & 1];
   p.rho = r->rho;
   p.part = r->part;
   p.ipart = r->ipart;
@@ -606,7 +671,7 @@ pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   hipLaunchKernelGGL(k_diag_particles<R>, dim3(2 * kDiagPartBlocks), dim3(kDiagThreads), 0, st, p);
   hipLaunchKernelGGL(k_diag_fields<R>, dim3(kDiagFieldBlocks), dim3(kDiagThreads), 0, st, p);
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagThreads), 0, st, r->part, r->ipart, r->budget,
-                     r->flags, r->step_dev, r->dout);
+                     r->flags, r->step_dev + (r->step & 1), r->dout);
   HIP_TRY(hipGetLastError());
   DiagOutDev o;
   HIP_TRY(hipMemcpyAsync(&o, r->dout, sizeof(o), hipMemcpyDeviceToHost, st));
@@ -670,7 +735,7 @@ struct pic_batch {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   // captured kernel nodes whose grid follows the resident work: kind 0 push,
-  // 1 field, 2 sort (hist and scatter), 3 persistent steps
+  // 1 field, 2 sort (hist and scatter), 3 persistent steps, 4 field and push
   std::vector<std::pair<hipGraphNode_t, int>> nodes;
   // asynchronous poll: step counters and the error word land in pinned host
   // memory behind the queued replays; a slot whose run changed since the
@@ -717,7 +782,7 @@ SlotDev<R> make_slot(const pic_batch* b, int slot, const pic_run* r, long long t
   }
   for (int pp = 0; pp < 2; ++pp)
     for (int fp = 0; fp < 2; ++fp) e.push[pp][fp] = make_push_args<R>(r, pp, fp, kBatchTile);
-  for (int fp = 0; fp < 2; ++fp) e.field[fp] = make_field_args<R>(r, fp, 0);
+  for (int fp = 0; fp < 2; ++fp) e.field[fp] = make_field_args<R>(r, fp, true);
   for (int q = 0; q < 2; ++q) e.sort[q] = make_sort_args<R>(r, q);
   for (int s = 0; s < 2; ++s) {
     e.cnt[s] = r->cnt[s];
@@ -804,10 +869,11 @@ pic_status capture_batch(pic_batch* b, hipStream_t st) {
     hipLaunchKernelGGL(k_steps_batch<R>, dim3(1), dim3(kThreads), 0, st, tab, b->start[0], b->start[3], n,
                        b->quantum, b->bar, b->err, b->bar_ticks);
   } else {
-    for (int q = 0; q < b->quantum; ++q) {
-      hipLaunchKernelGGL(k_push_batch<R>, dim3(1), dim3(kThreads), 0, st, tab, b->start[0], n);
-      hipLaunchKernelGGL(k_field_batch<R>, dim3(1), dim3(kFieldChunk), 0, st, tab, b->start[1], n);
-    }
+    // the fields of a step and the push of the next share a launch
+    hipLaunchKernelGGL(k_push_batch<R>, dim3(1), dim3(kThreads), 0, st, tab, b->start[0], n);
+    for (int q = 1; q < b->quantum; ++q)
+      hipLaunchKernelGGL(k_step_batch<R>, dim3(1), dim3(kThreads), 0, st, tab, b->start[0], b->start[3], n, q);
+    hipLaunchKernelGGL(k_field_batch<R>, dim3(1), dim3(kFieldChunk), 0, st, tab, b->start[1], n, b->quantum);
   }
   hipError_t e = hipStreamEndCapture(st, &b->graph);
   if (e != hipSuccess) return fail(PIC_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
@@ -822,6 +888,7 @@ pic_status capture_batch(pic_batch* b, hipStream_t st) {
   const void* fhist = reinterpret_cast<const void*>(&k_sort_hist_batch<R>);
   const void* fscat = reinterpret_cast<const void*>(&k_sort_scatter_batch<R>);
   const void* fsteps = reinterpret_cast<const void*>(&k_steps_batch<R>);
+  const void* fstep = reinterpret_cast<const void*>(&k_step_batch<R>);
   b->nodes.clear();
   for (hipGraphNode_t nd : all) {
     hipGraphNodeType ty;
@@ -830,7 +897,7 @@ pic_status capture_batch(pic_batch* b, hipStream_t st) {
     hipKernelNodeParams kp{};
     HIP_TRY(hipGraphKernelNodeGetParams(nd, &kp));
     const int kind = kp.func == fpush ? 0 : kp.func == ffield ? 1 : (kp.func == fhist || kp.func == fscat) ? 2
-                     : kp.func == fsteps ? 3 : -1;
+                     : kp.func == fsteps ? 3 : kp.func == fstep ? 4 : -1;
     if (kind >= 0) b->nodes.emplace_back(nd, kind);
   }
   return PIC_OK;
@@ -841,8 +908,9 @@ pic_status update_batch_grids(pic_batch* b) {
   if (!b->exec) return PIC_OK;
   // the persistent launch: enough work-groups for the larger pass, no more
   // than fit the device at once (its barriers need every one resident)
-  const int work[4] = {batch_work(b, 0), batch_work(b, 1), batch_work(b, 2),
-                       std::min(b->persist_cap, std::max(batch_work(b, 0), batch_work(b, 3)))};
+  const int work[5] = {batch_work(b, 0), batch_work(b, 1), batch_work(b, 2),
+                       std::min(b->persist_cap, std::max(batch_work(b, 0), batch_work(b, 3))),
+                       batch_work(b, 0) + batch_work(b, 3)};
   for (auto& nk : b->nodes) {
     hipKernelNodeParams kp{};
     HIP_TRY(hipGraphKernelNodeGetParams(nk.first, &kp));
@@ -1134,12 +1202,12 @@ pic_status pic_get_state(pic_run* r, pic_state* st, void* stream) {
     }
   }
   if (st->Ex_int)
-    HIP_TRY(hipMemcpy(st->Ex_int, r->Ex_int, (d.nx + 2) * sizeof(long long), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(st->Ex_int, r->Ex_int[r->step & 1], (d.nx + 2) * sizeof(long long), hipMemcpyDeviceToHost));
   int64_t* js[3] = {st->Jx_int, st->Jy_int, st->Jz_int};
   const size_t jl[3] = {(size_t)d.nx + 2, (size_t)d.nx + 3, (size_t)d.nx + 3};
   for (int k = 0; k < 3; ++k)
     if (js[k])
-      HIP_TRY(hipMemcpy(js[k], r->J[r->step & 1][k], jl[k] * sizeof(long long), hipMemcpyDeviceToHost));
+      HIP_TRY(hipMemcpy(js[k], j_buf(r, j_index(r, r->step), k), jl[k] * sizeof(long long), hipMemcpyDeviceToHost));
   st->step = r->step;
   {
     double bud[4];
@@ -1168,9 +1236,24 @@ pic_status pic_set_state(pic_run* r, const pic_state* st, void* stream) {
     if (po != pn) {
       HIP_TRY(hipMemcpy(r->FN[pn], r->FN[po], (size_t)(d.nx + 1) * 2 * rs, hipMemcpyDeviceToDevice));
       HIP_TRY(hipMemcpy(r->FH[pn], r->FH[po], (size_t)(d.nx + 2) * 4 * rs, hipMemcpyDeviceToDevice));
+      HIP_TRY(hipMemcpy(r->Ex_int[pn], r->Ex_int[po], (d.nx + 2) * sizeof(long long), hipMemcpyDeviceToDevice));
+    }
+    // the current of the step in progress moves with it, the others are clear
+    const int jo = j_index(r, r->step), jn = j_index(r, st->step);
+    if (jo != jn) {
+      const size_t jb = 3 * r->jstride * sizeof(unsigned long long);
+      HIP_TRY(hipMemcpy(j_buf(r, jn, 0), j_buf(r, jo, 0), jb, hipMemcpyDeviceToDevice));
+      for (int b = 0; b < 3; ++b)
+        if (b != jn) HIP_TRY(hipMemset(j_buf(r, b, 0), 0, jb));
     }
     r->step = st->step;
-    HIP_TRY(hipMemcpy(r->step_dev, &r->step, sizeof(long long), hipMemcpyHostToDevice));
+    const long long both[2] = {r->step, r->step};
+    HIP_TRY(hipMemcpy(r->step_dev, both, sizeof(both), hipMemcpyHostToDevice));
+    if (d.prec == PIC_FP32)
+      hipLaunchKernelGGL(k_incident<float>, dim3(1), dim3(1), 0, s, make_field_args<float>(r, 0, false), r->step);
+    else
+      hipLaunchKernelGGL(k_incident<double>, dim3(1), dim3(1), 0, s, make_field_args<double>(r, 0, false), r->step);
+    HIP_TRY(hipGetLastError());
   }
   for (int sp = 0; sp < 2; ++sp) {
     const pic_species_state& o = st->sp[sp];
@@ -1209,8 +1292,7 @@ pic_status pic_set_state(pic_run* r, const pic_state* st, void* stream) {
     }
     HIP_TRY(hipMemcpy(r->count + 2 * r->pp + sp, &n, sizeof(long long), hipMemcpyHostToDevice));
     r->n_max[sp] = n;
-    for (int p = 0; p < 2; ++p)
-      for (int k = 0; k < 3; ++k) HIP_TRY(hipMemset(r->J[p][k], 0, (d.nx + 3) * sizeof(long long)));
+    HIP_TRY(hipMemset(r->J, 0, 9 * r->jstride * sizeof(unsigned long long)));
   }
   {  // interleave the given fields into the current step's buffers
     const int p = (int)(r->step & 1);
@@ -1233,12 +1315,12 @@ pic_status pic_set_state(pic_run* r, const pic_state* st, void* stream) {
     }
   }
   if (st->Ex_int)
-    HIP_TRY(hipMemcpy(r->Ex_int, st->Ex_int, (d.nx + 2) * sizeof(long long), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(r->Ex_int[r->step & 1], st->Ex_int, (d.nx + 2) * sizeof(long long), hipMemcpyHostToDevice));
   const int64_t* js[3] = {st->Jx_int, st->Jy_int, st->Jz_int};
   const size_t jl[3] = {(size_t)d.nx + 2, (size_t)d.nx + 3, (size_t)d.nx + 3};
   for (int k = 0; k < 3; ++k)
     if (js[k])
-      HIP_TRY(hipMemcpy(r->J[r->step & 1][k], js[k], jl[k] * sizeof(long long), hipMemcpyHostToDevice));
+      HIP_TRY(hipMemcpy(j_buf(r, j_index(r, r->step), k), js[k], jl[k] * sizeof(long long), hipMemcpyHostToDevice));
   if (st->budget.valid) {
     const double bud[4] = {st->budget.E_in, st->budget.E_out_left, st->budget.E_out_right, 0.0};
     HIP_TRY(hipMemcpy(r->budget, bud, sizeof(bud), hipMemcpyHostToDevice));
@@ -1656,6 +1738,10 @@ pic_status pic_batch_release(pic_batch* b, int32_t slot, void* stream) {
   r->pp = step > 0 ? (int)(((step - 1) / r->cfg.sort_interval) & 1) : 0;
   r->batch = nullptr;
   HIP_TRY(hipMemsetAsync(r->tpred, 0, 2 * sizeof(int), st));  // single-run tiles from here
+  // the counter of both step parities, and the currents (the batch kept the
+  // one and rotated the others)
+  hipLaunchKernelGGL(k_set_counts, dim3(1), dim3(1), 0, st, r->step_dev, step, step);
+  HIP_TRY(hipMemsetAsync(r->J, 0, 9 * r->jstride * sizeof(unsigned long long), st));
   b->runs[slot] = nullptr;
   ++b->gen[slot];
   b->target[slot] = 0;
