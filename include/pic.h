@@ -331,7 +331,8 @@ pic_status pic_track(const pic_wave* wave, int32_t scheme, int32_t rr, int32_t p
  * plus FMA corrections): for every float whose bit pattern lies in
  * [first, first + count) and that is finite and >= 1, compare with the
  * compiler's correctly rounded sqrtf and 1.0f / x (the reciprocal below 2^126
- * only) and add the number of differing results to *d_mismatches, a device
+ * only), and their FP64 forms at a double of the same leading bits with
+ * sqrt and 1.0 / x, and add the number of differing results to *d_mismatches, a device
  * counter the caller zeroes and reads.  Asynchronous on stream; first + count
  * above 2^32 is PIC_EINVAL. */
 pic_status pic_check_rounding(uint32_t first, uint32_t count, unsigned long long* d_mismatches,

@@ -161,12 +161,16 @@ __device__ __forceinline__ const T& kernel_args() {
 
 // Approximate (about 1 ulp) reciprocal, reciprocal square root and square
 // root for the Boris and RR arithmetic; the contract lines use IEEE ops.
+// In FP64 they are correctly rounded (rsq: the reciprocal of the root), by
+// the routines below; every argument is at least 1 there too.
+__device__ __forceinline__ double sqrt_rn_ge1(double x);
+__device__ __forceinline__ double rcp_rn_ge1(double x);
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsq(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double rsq(double x) { return rcp_rn_ge1(sqrt_rn_ge1(x)); }
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
+__device__ __forceinline__ double rcp(double x) { return rcp_rn_ge1(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double fsqrt(double x) { return sqrt(x); }
+__device__ __forceinline__ double fsqrt(double x) { return sqrt_rn_ge1(x); }
 
 // Element i of an array at a wave-uniform base: a 32-bit byte offset added
 // to the 64-bit base lets the compiler use scalar-base addressing instead of
@@ -289,8 +293,29 @@ __device__ __forceinline__ float rcp_rn_ge1(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
-__device__ __forceinline__ double sqrt_rn_ge1(double x) { return sqrt(x); }
-__device__ __forceinline__ double rcp_rn_ge1(double x) { return 1.0 / x; }
+// In FP64: the coupled Newton (Goldschmidt) iteration for sqrt(x) and
+// 1 / (2 sqrt(x)) from the hardware estimate, then two residual corrections;
+// two Newton steps and one residual correction of the reciprocal.  The
+// general sqrt and division also scale their operands for the ends of the
+// exponent range and sort out special values: 7 and 4 more instructions of 17
+// and 11, some 40 of the 370 an average FP64 push issues.  Finite arguments
+// in [1, 2^1000] need none of it; infinities and NaN give NaN, which the
+// callers drop as they drop infinity (a momentum past 1e30).
+__device__ __forceinline__ double sqrt_rn_ge1(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double s = x * y, h = 0.5 * y;
+  const double r = fma(-h, s, 0.5);
+  h = fma(h, r, h);
+  s = fma(s, r, s);
+  s = fma(fma(-s, s, x), h, s);
+  return fma(fma(-s, s, x), h, s);
+}
+__device__ __forceinline__ double rcp_rn_ge1(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
 
 // Position update of the deposition contract: gamma from the stored
 // momentum in the order ((1 + ux^2) + uy^2) + uz^2, correctly rounded square
@@ -1737,9 +1762,19 @@ __global__ void k_track_rk4(TrackArgs a) {
 }
 
 // ---------------------------------------------------------------- self-check
+__device__ __forceinline__ unsigned long long splitmix64(unsigned long long seed,
+                                                         unsigned long long i) {
+  unsigned long long z = seed + (i + 1ull) * 0x9E3779B97F4A7C15ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  return z ^ (z >> 31);
+}
+
 // Floats with bit patterns first .. first + count - 1 (those >= 1): count the
 // results of sqrt_rn_ge1 and rcp_rn_ge1 (below 2^126) that differ from the
-// correctly rounded sqrtf and 1.0f / x.
+// correctly rounded sqrtf and 1.0f / x; and, for a double of the same leading
+// bits with the other 29 drawn from a hash of them, of their FP64 forms that
+// differ from sqrt and 1.0 / x.
 __global__ void k_check_rounding(unsigned first, unsigned count, unsigned long long* bad) {
   unsigned long long mine = 0;
   const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
@@ -1748,6 +1783,10 @@ __global__ void k_check_rounding(unsigned first, unsigned count, unsigned long l
     if (!(x >= 1.0f) || !(x <= 3.4028235e38f)) continue;
     mine += __float_as_uint(sqrt_rn_ge1(x)) != __float_as_uint(sqrtf(x));
     if (x < 0x1p126f) mine += __float_as_uint(rcp_rn_ge1(x)) != __float_as_uint(1.0f / x);
+    const double d = __longlong_as_double(__double_as_longlong((double)x) |
+                                          (long long)(splitmix64(0ull, first + k) >> 35));
+    mine += __double_as_longlong(sqrt_rn_ge1(d)) != __double_as_longlong(sqrt(d));
+    mine += __double_as_longlong(rcp_rn_ge1(d)) != __double_as_longlong(1.0 / d);
   }
   if (mine) atomicAdd(bad, mine);
 }
@@ -2064,14 +2103,6 @@ __global__ __launch_bounds__(kThreads, PIC_STEPS_MIN_WAVES) void k_steps_batch(c
 }
 
 // ---------------------------------------------------------------- init
-__device__ __forceinline__ unsigned long long splitmix64(unsigned long long seed,
-                                                         unsigned long long i) {
-  unsigned long long z = seed + (i + 1ull) * 0x9E3779B97F4A7C15ull;
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  return z ^ (z >> 31);
-}
-
 template <typename R>
 __global__ void k_init(SpeciesDev<R> e, SpeciesDev<R> ion, long long n, int c0, int ppc,
                        unsigned long long seed, double jitter, R w) {
