@@ -58,7 +58,12 @@ constexpr int kBatchTile = kThreads * kBatchPPT;
 // The batched push keeps two particles' loads in flight per thread rather
 // than the whole tile's: fewer registers, six waves per SIMD instead of five.
 constexpr int kBatchDepth = PIC_BATCH_DEPTH;
-constexpr int kMinTile = kTile < kBatchTile ? kTile : kBatchTile;
+// Smallest tile of a run of `cap` particles per species (its per-tile arrays
+// are sized for it): one particle per thread for up to 2^16, two for up to
+// 2^17, else the batched push's; see small_tile().
+constexpr int min_tile(long long cap) {
+  return cap <= 1 << 16 ? kThreads : cap <= 1 << 17 ? 2 * kThreads : kTile < kBatchTile ? kTile : kBatchTile;
+}
 constexpr int kLdsSlots = PIC_PUSH_LDS_SLOTS;  // 64-bit LDS current accumulators per work-group
 constexpr int kDepth = PIC_PUSH_DEPTH;        // particles per thread whose loads are in flight
 constexpr int kRingUnroll = PIC_RING_UNROLL;  // ring turns per loop iteration (renames, no copies)
@@ -1301,14 +1306,15 @@ __global__ PIC_PUSH_BOUNDS void k_push(PushArgs<R>) {
   push_one_tile<R, kPPT, kDepth>(a, a.tile0 + (int)blockIdx.x, jw, lds);
 }
 
-// the same push in tiles of kBatchTile (two particles' loads in flight, as
-// in the batched push), for runs too small to fill the device with kTile tiles
-template <typename R>
+// the same push in tiles of PPT particles per thread (two particles' loads in
+// flight, as in the batched push), for runs too small to fill the device with
+// kTile tiles
+template <typename R, int PPT>
 __global__ PIC_PUSH_BOUNDS void k_push_small(PushArgs<R>) {
   const PushArgs<R>& a = kernel_args<PushArgs<R>>();
   __shared__ __align__(16) unsigned long long lds[kLdsSlots];
   const int jw = j_buffer(a.jfix, a.jfix >= 0 ? 0 : *a.step);
-  push_one_tile<R, kBatchPPT, kBatchDepth>(a, a.tile0 + (int)blockIdx.x, jw, lds);
+  push_one_tile<R, PPT, (PPT > 1 ? kBatchDepth : 1)>(a, a.tile0 + (int)blockIdx.x, jw, lds);
 }
 
 // One launch per step for small runs: the field pass of step n (f) and the
@@ -1327,7 +1333,7 @@ struct StepArgs {
   FieldArgs<R> f;
 };
 
-template <typename R>
+template <typename R, int PPT>
 __global__ PIC_PUSH_BOUNDS void k_step(StepArgs<R>) {
   const PushArgs<R>& a = kernel_args<StepArgs<R>>().a;
   const FieldArgs<R>& f = kernel_args<StepArgs<R>>().f;
@@ -1337,7 +1343,7 @@ __global__ PIC_PUSH_BOUNDS void k_step(StepArgs<R>) {
   const int jr = j_buffer(-1, n), jw = jr == 2 ? 0 : jr + 1;
   const int b = (int)blockIdx.x;
   if (b < a.ntiles)
-    push_one_tile<R, kBatchPPT, kBatchDepth, true>(a, b, jw, lds, &f, n, jr);
+    push_one_tile<R, PPT, (PPT > 1 ? kBatchDepth : 1), true>(a, b, jw, lds, &f, n, jr);
   else
     field_chunk<R, kThreads>(f, b - a.ntiles, n, jr, reinterpret_cast<R*>(lds));
 }

@@ -162,7 +162,7 @@ struct pic_run {
   DiagOutDev* dout;
   unsigned long long* hist;
   int tiles_max;
-  int push_tile = kTile;  // particles per push work-group: kTile, or kBatchTile for small runs
+  int push_tile = kTile;  // particles per push work-group: kTile, or small_tile()
   struct pic_batch* batch = nullptr;  // set while the run is stepped by a batch
   // pic_step replays two sort intervals at a time as one captured graph (the
   // kernel arguments repeat with that period: step parity and sort parity
@@ -216,7 +216,8 @@ void carve(pic_run* r, Carver& cv) {
   r->count = cv.take<long long>(4);
   r->step_dev = cv.take<long long>(2);
   r->flags = cv.take<int>(4);
-  r->tiles_max = 2 * tiles_for(d.cap, kMinTile);  // a run may also step in a batch
+  // (a run may also step in a batch)
+  r->tiles_max = 2 * tiles_for(d.cap, min_tile(d.cap));
   r->acc = cv.take<double>(4 * (size_t)std::max(r->tiles_max, 1));
   r->trange = cv.take<int>(4 * (size_t)std::max(r->tiles_max, 1));
   r->tpred = cv.take<int>(2);
@@ -308,6 +309,20 @@ bool comp_on(const pic_run* r) {
 
 int sort_blocks_for(long long n) {
   return (int)std::max<long long>(1, (n + kSortTile - 1) / kSortTile);
+}
+
+// Tile of a run too small for kTile: the smallest of one, two and four
+// particles per thread that gives at most two tiles per compute unit.  Below
+// that a tile's serial chain of particles is the step's time, above it the
+// set-up of the many tiles.  Time per step in us at one / two / four per
+// thread, 256 compute units: 51,200 particles 8.0 / 9.0 / 10.5, 102,400 9.0 /
+// 9.1 / 10.7, 204,800 11.8 / 10.3 / 11.1, 409,600 20.5 / 14.2 / 13.0 (FP32; in
+// FP64 8.2 / 9.4 / 11.1, 9.4 / 9.6 / 11.4, 12.7 / 11.3 / 12.2, 22.0 / 16.0 / 14.3).
+int small_tile(const Derived& d, int cus) {
+  static_assert(kBatchPPT == 4, "small tiles of one, two and four particles per thread");
+  for (int tile = min_tile(d.cap); tile < kBatchTile; tile *= 2)
+    if (2 * tiles_for(d.n_foil, tile) <= 2 * cus) return tile;
+  return kBatchTile;
 }
 
 // Runs in small tiles advance a step's fields and push the next in one
@@ -437,15 +452,15 @@ pic_status launch_push(pic_run* r, hipStream_t st, bool capture = false) {
   split_launch(a.ntiles, r->max_grid, [&](int t0, int n, bool first, bool last) {
     a.tile0 = t0;
     hipEvent_t s0 = first ? e0 : nullptr, s1 = last ? e1 : nullptr;
-    const bool small = r->push_tile == kBatchTile;
-    if (capture && small)  // (recorded launches carry no events)
-      hipLaunchKernelGGL(k_push_small<R>, dim3(n), dim3(kThreads), 0, st, a);
-    else if (capture)
-      hipLaunchKernelGGL(k_push<R>, dim3(n), dim3(kThreads), 0, st, a);
-    else if (small)
-      hipExtLaunchKernelGGL(k_push_small<R>, dim3(n), dim3(kThreads), 0, st, s0, s1, 0, a);
+    const int ppt = r->push_tile / kThreads;
+    auto* k = r->push_tile == kTile ? k_push<R>
+              : ppt == 1            ? k_push_small<R, 1>
+              : ppt == 2            ? k_push_small<R, 2>
+                                    : k_push_small<R, kBatchPPT>;
+    if (capture)  // (recorded launches carry no events)
+      hipLaunchKernelGGL(k, dim3(n), dim3(kThreads), 0, st, a);
     else
-      hipExtLaunchKernelGGL(k_push<R>, dim3(n), dim3(kThreads), 0, st, s0, s1, 0, a);
+      hipExtLaunchKernelGGL(k, dim3(n), dim3(kThreads), 0, st, s0, s1, 0, a);
   });
   HIP_TRY(hipGetLastError());
   if (!capture) ev_done(r, slot);
@@ -512,7 +527,9 @@ pic_status launch_step(pic_run* r, hipStream_t st) {
   const int p = (int)(r->step & 1);
   const StepArgs<R> s{make_push_args<R>(r, r->pp, p ^ 1, r->push_tile), make_field_args<R>(r, p, false)};
   const int chunks = (r->d.nx + 3 + kThreads - 1) / kThreads;
-  hipLaunchKernelGGL(k_step<R>, dim3(s.a.ntiles + chunks), dim3(kThreads), 0, st, s);
+  const int ppt = r->push_tile / kThreads;
+  auto* k = ppt == 1 ? k_step<R, 1> : ppt == 2 ? k_step<R, 2> : k_step<R, kBatchPPT>;
+  hipLaunchKernelGGL(k, dim3(s.a.ntiles + chunks), dim3(kThreads), 0, st, s);
   HIP_TRY(hipGetLastError());
   r->step += 1;
   return PIC_OK;
@@ -1033,16 +1050,16 @@ pic_status pic_init(const pic_config* cfg, void* d_ws, size_t ws_bytes, void* st
   r->n_max[0] = r->n_max[1] = r->d.n_foil;
   r->step = 0;
   r->pp = 0;
-  // Small runs push in tiles of kBatchTile: with fewer than two large tiles
-  // per compute unit the large tiles leave most of the device idle (on
-  // 4e5 particles the small tiles push 1.85x faster, on 1e7 the large ones
+  // Small runs push in small tiles: with fewer than two large tiles per
+  // compute unit the large tiles leave most of the device idle (on 4e5
+  // particles the small tiles push 1.85x faster, on 1e7 the large ones
   // 1.27x).  Fixed for the run: the push's window predictions are per tile.
   {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
         2 * tiles_for(r->d.n_foil) < 2 * cus)  // both species' large tiles
-      r->push_tile = kBatchTile;
+      r->push_tile = small_tile(r->d, cus);
   }
   hipStream_t s = S(stream);
   hipError_t e = hipMemsetAsync(d_ws, 0, cv.off, s);

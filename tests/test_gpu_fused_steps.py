@@ -27,21 +27,25 @@ def _fields(rng, nx, rdt):
 
 
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("tile", [256, 512, 1024])
 @pytest.mark.parametrize("n,lo,hi,order", [
     (1, 5, 6, True), (1023, 0, 3, True), (1025, 1997, 2000, True), (5000, 0, 2000, True),
     (3000, 0, 2000, False),     # unsorted: every tile spans the box
     (2100, 700, 1040, False),   # about the widest tile that fits in FP64
     (2100, 700, 1210, False),   # and in FP32
     (9000, 0, 1, True)])
-def test_fused_steps_match_stages(precision, n, lo, hi, order):
+def test_fused_steps_match_stages(precision, tile, n, lo, hi, order):
     from paper_1008_1685_amd import Run
 
-    print(f"\n[gpu] fused {precision} {n} [{lo}, {hi}) {order}", flush=True)
-    cfg = preset("c1", precision=precision, ppc=1, thickness=0.01, sort_interval=4, pol="CP")
+    print(f"\n[gpu] fused {precision} tile {tile} {n} [{lo}, {hi}) {order}", flush=True)
+    # (the quiet start only chooses the tile: the state replaces it)
+    cfg = preset("c1", precision=precision, ppc={256: 1, 512: 100000, 1024: 200000}[tile], thickness=0.01,
+                 sort_interval=4, pol="CP")
     runs, out = [], []
     for _ in range(2):
         rng = np.random.default_rng(n + lo)
         r = Run(cfg, capacity=n)
+        assert r.info["tile"] == tile
         nx = r.info["n_cells"]
         part = _state(rng, n, lo, hi, nx, r.rdt, order)
         r.set_state(particles={0: part(5.0, r.info["w_ref"]), 1: part(0.1, 0.7 * r.info["w_ref"])},
