@@ -71,10 +71,11 @@ extern "C" {
 #endif
 
 /* Field advance kernels.  TILES: work-groups of 8 columns x 32 rows, each
- * loading its tile with halos into LDS; any period.  STRIPS: a work-group
- * owns a strip of columns and the whole period (one thread per row, at most
- * 1024 rows in FP32, 512 in FP64) and marches along x, reading every value
- * once; automatic where it fits. */
+ * loading its tile with halos into LDS; any period.  STRIPS: each wave
+ * owns a strip of columns of up to 61 rows and marches along x, reading every
+ * value once and skipping the currents of columns that hold none; the
+ * automatic choice (asked for by name: at most 1024 rows in FP32, 512 in
+ * FP64). */
 #define PIC2D_FIELD_TILES 1
 #define PIC2D_FIELD_STRIPS 2
 

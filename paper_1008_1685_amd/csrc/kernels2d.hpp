@@ -16,10 +16,9 @@
 //               with halos recomputed in LDS, boundary guards, Poynting
 //               bookkeeping, the running integer charge implied by the
 //               current, and the clearing of the next step's current.
-//   k_field2m   the same step in column-marching form: a work-group owns a
-//               strip of columns and the whole period (one thread per row)
-//               and streams along x, reading each value once; used where
-//               the period fits one work-group.
+//   k_field2s   the same step in column-marching form: each wave streams a
+//               strip of columns along x by itself, reading each value once,
+//               and skips the currents of columns no push added to.
 //   k_init2, k_diag2_*: quiet start and FP64 diagnostics.
 // The cell sort reuses the 1D kernels (the y offset moves with the particle).
 //
@@ -95,6 +94,11 @@ struct Push2Args {
   int comp;
   R sw;                         // 256 / w_ref
   int qw_ref[2];
+  // Current columns this step adds to: column k of the current arrays is
+  // stamped with the step before anything is added to it, so that the field
+  // pass need not read the other columns or clear them again.
+  int* act;                     // [nx + 3]
+  int stamp;
 };
 
 template <typename R>
@@ -501,6 +505,7 @@ __device__ __forceinline__ void push2_pass(const Push2Args<R>& a, const SpeciesD
   const int tid = threadIdx.x, lane = tid & 63;
   const int ny = a.ny;
   const int xmn = rg.xmn, xmx = rg.xmx, span = rg.dmx - rg.dmn + 4;
+  for (int k = tid; k < xmx - xmn + 4; k += kThreads) a.act[xmn + k] = a.stamp;
   Box2 bx;
   bx.xmn = xmn;
   bx.BX = xmx - xmn + 4;
@@ -760,6 +765,8 @@ struct Field2Args {
   double* flux;                   // [3][ny] per row: E_in, E_out_left, E_out_right
   long long* step_dev;            // device step counter, set to step + 1
   long long step;                 // this step (the laser clock)
+  const int* act;                 // [nx + 3] columns stamped by the pushes into J (this step's stamp) and
+  const int* act_next;            // into Jnext (the step before's): the others hold zeros
   int nx, ny;
   R a, ha, dt;                    // dt/dx, dt/(2 dx), dt
   double dtd, dy;
@@ -934,36 +941,57 @@ __global__ __launch_bounds__(256) void k_field2(Field2Args<R> p) {
   }
 }
 
-// One Yee step, column-marching form, for periods of at most kFMRows<R>
-// rows: a work-group owns all ny rows (one thread each) of a strip of
-// columns [Xs, Xe) and walks along x.  At column c it forms B^{n+1/2} at c,
-// E^{n+1} at c - 1 and B^{n+1} at c - 2 (with the outputs, running charge
-// and next current of that column), while the loads of column c + 1 are in
-// flight.  Every value is read once, plus the three columns a strip shares
-// with its neighbours.  The row neighbours j + 1 and j - 1 (periodic) pass
-// through LDS slots indexed by row, double-buffered by column parity, so
-// one barrier per column orders them.  The arithmetic is that of k_field2,
-// term by term.
-template <typename R>
-constexpr int kFMRows = sizeof(R) == 4 ? 1024 : 512;
+// One Yee step, column-marching form: every wave by itself owns up to
+// kFSRows rows (one lane per row, with one row below and two above recomputed)
+// of a strip of columns [Xs, Xe) and walks along x.  At column c it forms
+// B^{n+1/2} at c, E^{n+1} at c - 1 and B^{n+1} at c - 2 (with the outputs,
+// running charge and next current of that column), while the loads of column
+// c + 1 are in flight.  The row neighbours j + 1 and j - 1 come from the
+// neighbouring lanes by DPP, so that no wave waits for another; every value
+// is read once, plus the three rows and columns a wave shares with its
+// neighbours.  Columns no push has added to hold no current: it is neither
+// read nor cleared there, and the running charge stays (64 of the 112 B a
+// cell moves; a plasma fills a small part of its box).  HBM-bound on large
+// grids, the latency of a strip on small ones.  The arithmetic is that of
+// k_field2, term by term, with the fused multiply-adds written out.
+constexpr int kFSRows = kLanes - 3;
+constexpr int kFSMaxCols = kLanes - 6;  // columns per strip: with its halos one bit each of a wave mask
 
-template <typename R>
-__host__ __device__ constexpr size_t field2m_lds(int ny) {
-  return 2 * (size_t)ny * (6 * sizeof(R) + sizeof(long long));
+__device__ __forceinline__ int lane_below(int v) {  // lane i: the value of lane i - 1
+  return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false);
 }
+__device__ __forceinline__ int lane_above(int v) {  // lane i: the value of lane i + 1
+  return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, false);
+}
+__device__ __forceinline__ float lane_below(float v) { return __int_as_float(lane_below(__float_as_int(v))); }
+__device__ __forceinline__ float lane_above(float v) { return __int_as_float(lane_above(__float_as_int(v))); }
+__device__ __forceinline__ long long lane_below(long long v) {
+  const unsigned lo = (unsigned)lane_below((int)(unsigned)v), hi = (unsigned)lane_below((int)(unsigned)(v >> 32));
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ long long lane_above(long long v) {
+  const unsigned lo = (unsigned)lane_above((int)(unsigned)v), hi = (unsigned)lane_above((int)(unsigned)(v >> 32));
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_below(double v) { return __longlong_as_double(lane_below(__double_as_longlong(v))); }
+__device__ __forceinline__ double lane_above(double v) { return __longlong_as_double(lane_above(__double_as_longlong(v))); }
 
+// rows: outputs per wave (at most kFSRows); groups: waves over the period;
+// strips: strips of columns.  Wave w of the grid takes rows w mod groups of
+// strip w / groups.
 template <typename R>
-__global__ __launch_bounds__(kFMRows<R>) void k_field2m(Field2Args<R> p) {
-  extern __shared__ __align__(16) unsigned char fsm[];
-  const int n = p.nx, ny = p.ny, j = threadIdx.x;
-  const bool live = j < ny;
-  const int jp = j + 1 >= ny ? 0 : j + 1, jm = !live ? 0 : (j == 0 ? ny - 1 : j - 1);
-  // strip of this block: columns [Xs, Xe), widths differing by at most one
-  const int nb = gridDim.x, s = blockIdx.x, ncol = n + 2;
-  const int Xs = (int)((long long)s * ncol / nb), Xe = (int)((long long)(s + 1) * ncol / nb);
-  if (s == 0 && j == 0) *p.step_dev = p.step + 1;
-  R* xr = (R*)fsm;                                              // [2][6][ny]
-  long long* xj = (long long*)(fsm + 2 * 6 * (size_t)ny * sizeof(R));  // [2][ny]
+__global__ __launch_bounds__(256) void k_field2s(Field2Args<R> p, int rows, int groups, int strips) {
+  const int n = p.nx, ny = p.ny, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+  if (w == 0 && lane == 0) *p.step_dev = p.step + 1;
+  const int s = w / groups, g = w - s * groups;
+  if (s >= strips) return;
+  const int ncol = n + 2;
+  const int Xs = (int)((long long)s * ncol / strips), Xe = (int)((long long)(s + 1) * ncol / strips);
+  int j = g * rows - 1 + lane;  // rows g rows - 1 .. + 62, of which lanes 1 .. rows are output
+  const bool live = lane >= 1 && lane <= rows && j < ny;
+  if (j < 0) j += ny;
+  if (j >= ny) j %= ny;
   const R a = p.a, ha = p.ha, dt = p.dt, z = R(0);
   // column state, by age at the top of the iteration for column c:
   R ex0 = z, ey0 = z, ez0 = z, bx0 = z, by0c = z, bz0c = z;   // E^n, B^n (c)
@@ -982,15 +1010,22 @@ __global__ __launch_bounds__(kFMRows<R>) void k_field2m(Field2Args<R> p) {
   NH<R> fnh{z, z};
   HN<R> fhn{z, z};
   long long fj0 = 0, fj1 = 0, fj2 = 0, fcn = 0;
-  auto load_col = [&](int col) {
+  // columns Xs - 2 .. Xs + 61: current stamped this step (J), the step before (Jnext)
+  const int col0 = Xs - 2;
+  const bool inside = col0 + lane >= 0 && col0 + lane <= n + 2;
+  const unsigned long long m_now = __ballot(inside && p.act[inside ? col0 + lane : 0] == (int)p.step);
+  const unsigned long long m_old = __ballot(inside && p.act_next[inside ? col0 + lane : 0] == (int)p.step - 1);
+  auto now = [&](int col) { return (m_now >> (col - col0)) & 1ull; };
+  auto old = [&](int col) { return (m_old >> (col - col0)) & 1ull; };
+  auto load_col = [&](int col) {  // (wave-uniform conditions)
     const bool nd = col >= 0 && col <= n, hf = col >= 0 && col <= n + 1;
     const size_t gi = (size_t)(col < 0 ? 0 : col) * ny + j;
-    fez = live && nd ? p.in.ez[gi] : z;
-    fnh = live && nd ? p.in.nh[gi] : NH<R>{z, z};
-    fhn = live && hf ? p.in.hn[gi] : HN<R>{z, z};
-    fbz = live && hf ? p.in.bz[gi] : z;
-    fj0 = live && hf ? p.J[0][gi] : 0;
-    const bool jy = live && col >= -1 && col <= n + 1;
+    fez = nd ? p.in.ez[gi] : z;
+    fnh = nd ? p.in.nh[gi] : NH<R>{z, z};
+    fhn = hf ? p.in.hn[gi] : HN<R>{z, z};
+    fbz = hf ? p.in.bz[gi] : z;
+    fj0 = hf && now(col) ? p.J[0][gi] : 0;
+    const bool jy = col >= -1 && col <= n + 1 && now(col + 1);
     const size_t gk = (size_t)(col + 1 < 0 ? 0 : col + 1) * ny + j;
     fj1 = jy ? p.J[1][gk] : 0;
     fj2 = jy ? p.J[2][gk] : 0;
@@ -1001,89 +1036,80 @@ __global__ __launch_bounds__(kFMRows<R>) void k_field2m(Field2Args<R> p) {
   const double th = ((double)p.step + 0.5) * p.dtd;
   for (int c = Xs - 2; c <= Xe + 1; ++c) {
     // loads for the next iterations: E^n, B^n, J of column c + 1 (needed up
-    // to column Xe), the running charge of column c - 1 (output next)
+    // to column Xe), the running charge of column c - 1 (output next) where
+    // a current changes it
     if (c + 1 <= Xe) load_col(c + 1);
     const int xo = c - 1;  // output column of the next iteration
-    fcn = live && xo >= Xs && xo < Xe && xo <= n ? p.cont[(size_t)xo * ny + j] : 0;
-    // publish the values rows j - 1 and j + 1 take from this row
-    R* X = xr + (size_t)(c & 1) * 6 * ny;
-    long long* XJ = xj + (size_t)(c & 1) * ny;
-    if (live) {
-      X[j] = ex0;
-      X[ny + j] = ez0;
-      X[2 * ny + j] = hbz1;
-      X[3 * ny + j] = hbx1;
-      X[4 * ny + j] = nex2;
-      X[5 * ny + j] = nez2;
-      XJ[j] = jq1;
-    }
-    __syncthreads();
-    const R exn = X[jp], ezn = X[ny + jp];           // E^n (c) at j + 1
-    const R hbzm = X[2 * ny + jm], hbxm = X[3 * ny + jm];  // B^{n+1/2} (c - 1) at j - 1
-    const R nexn = X[4 * ny + jp], nezn = X[5 * ny + jp];  // E^{n+1} (c - 2) at j + 1
-    const long long j1m = XJ[jm];                    // J_y (c - 2) at j - 1
+    fcn = xo >= Xs && xo < Xe && xo <= n && (now(xo) | now(xo + 1)) ? p.cont[(size_t)xo * ny + j] : 0;
+    const R exn = lane_above(ex0), ezn = lane_above(ez0);       // E^n (c) at j + 1
+    const R hbzm = lane_below(hbz1), hbxm = lane_below(hbx1);   // B^{n+1/2} (c - 1) at j - 1
+    const R nexn = lane_above(nex2), nezn = lane_above(nez2);   // E^{n+1} (c - 2) at j + 1
+    const long long j1m = lane_below(jq1);                      // J_y (c - 2) at j - 1
     // B^{n+1/2} at column c
     R hbz0 = bz0c, hby0 = by0c, hbx0 = bx0;
     if (c >= 1 && c <= n) {
-      hbz0 -= ha * ((ey0 - ey1) - (exn - ex0));
-      hby0 += ha * (ez0 - ez1);
+      hbz0 = fma(-ha, (ey0 - ey1) - (exn - ex0), hbz0);
+      hby0 = fma(ha, ez0 - ez1, hby0);
     }
-    if (c >= 0 && c <= n) hbx0 -= ha * (ezn - ez0);
+    if (c >= 0 && c <= n) hbx0 = fma(-ha, ezn - ez0, hbx0);
     // E^{n+1} at column c - 1
     R nex1 = z, ney1 = z, nez1 = z;
     const int Xn = c - 1;
     if (Xn >= Xs - 1 && Xn <= Xe - 1) {
       const R jx = (R)((double)jp0 * p.sJ), jy = (R)((double)jp1 * p.sJ);
       const R jz = (R)((double)jp2 * p.sJz);
-      nex1 = (Xn >= 1 && Xn <= n) ? ex1 + (a * (hbz1 - hbzm) - dt * jx) : ex1;
+      nex1 = (Xn >= 1 && Xn <= n) ? ex1 + fma(a, hbz1 - hbzm, -(dt * jx)) : ex1;
       if (Xn >= 0 && Xn <= n) {
         R bz0 = hbz1, bz1 = hbz0, by0 = hby1, by1 = hby0;
-        const R ey = ey1, ez = ez1, d = R(1) + a;
+        const R ey = ey1, ez = ez1;
         if (Xn == 0) {
           const double env = envelope(th, p.tr, p.tf, p.tl);
           ey_in = p.ay * env * sin(th) * profile2((j + 0.5) * p.dy, p.yc, p.waist);
           ez_in = p.az * env * cos(th) * profile2((double)j * p.dy, p.yc, p.waist);
-          bz0 = (R(4) * (R)ey_in - R(2) * ey - (R(1) - a) * bz1 + dt * jy) / d;
-          by0 = (R(2) * ez - (R(1) - a) * by1 - dt * jz - R(4) * (R)ez_in) / d;
+          guard_left<R>(a, dt, ey, ez, bz1, by1, jy, jz, ey_in, ez_in, bz0, by0);
           gl0 = bz0;
           gl1 = by0;
         }
         if (Xn == n) {
-          bz1 = (R(2) * ey - (R(1) - a) * bz0 - dt * jy) / d;
-          by1 = (R(-2) * ez - (R(1) - a) * by0 + dt * jz) / d;
+          guard_right<R>(a, dt, ey, ez, bz0, by0, jy, jz, bz1, by1);
           gr0 = bz1;
           gr1 = by1;
         }
-        ney1 = ey - (a * (bz1 - bz0) + dt * jy);
-        nez1 = ez + (a * ((by1 - by0) - (hbx1 - hbxm)) - dt * jz);
+        ney1 = ey - fma(a, bz1 - bz0, dt * jy);
+        nez1 = ez + fma(a, (by1 - by0) - (hbx1 - hbxm), -(dt * jz));
       }
     }
     // B^{n+1} and the outputs at column c - 2
     const int Xo = c - 2;
-    if (live && Xo >= Xs && Xo < Xe) {
+    if (Xo >= Xs && Xo < Xe && live) {
       const size_t gi = (size_t)Xo * ny + j;
       R bz, by;
       if (Xo >= 1 && Xo <= n) {
-        bz = hbz2 - ha * ((ney2 - ney3) - (nexn - nex2));
-        by = hby2 + ha * (nez2 - nez3);
+        bz = fma(-ha, (ney2 - ney3) - (nexn - nex2), hbz2);
+        by = fma(ha, nez2 - nez3, hby2);
       } else {  // guards keep their t_{n+1/2} value
         bz = Xo == 0 ? gl0 : gr0;
         by = Xo == 0 ? gl1 : gr1;
       }
       p.out.bz[gi] = bz;
       p.out.hn[gi] = HN<R>{nex2, by};
-      p.Jnext[0][gi] = 0ull;
-      p.Jnext[1][gi] = 0ull;
-      p.Jnext[2][gi] = 0ull;
+      if (old(Xo)) {
+        p.Jnext[0][gi] = 0ull;
+        p.Jnext[1][gi] = 0ull;
+        p.Jnext[2][gi] = 0ull;
+      }
       if (Xo == n + 1) {
-        p.Jnext[1][gi + ny] = 0ull;
-        p.Jnext[2][gi + ny] = 0ull;
+        if (old(n + 2)) {
+          p.Jnext[1][gi + ny] = 0ull;
+          p.Jnext[2][gi + ny] = 0ull;
+        }
       } else {
-        const R bx = hbx2 - ha * (nezn - nez2);
         p.out.ez[gi] = nez2;
-        p.out.nh[gi] = NH<R>{ney2, bx};
-        const long long div = (jp0 - jq0) + (jq1 - j1m);
-        p.cont[gi] = cn2 - div;
+        p.out.nh[gi] = NH<R>{ney2, fma(-ha, nezn - nez2, hbx2)};
+        if (now(Xo) | now(Xo + 1)) {
+          const long long div = (jp0 - jq0) + (jq1 - j1m);
+          p.cont[gi] = cn2 - div;
+        }
         if (Xo == 0) {
           const double eyl = 0.5 * ((double)ey2 + (double)ney2), ezl = 0.5 * ((double)ez2 + (double)nez2);
           const double bzl = 0.5 * ((double)gl0 + (double)hbz1);
