@@ -113,7 +113,8 @@ typedef struct pic2d_info {
   int64_t capacity;          /* per species */
   int64_t n_init[2];
   int64_t step;
-  int32_t tile;              /* particles per push work-group */
+  int32_t tile;              /* particles per push work-group: 256, 512 or 1024, by the foil's count
+                                and the capacity */
   int32_t lds_slots;         /* 64-bit LDS current accumulators per push work-group */
   int32_t field_kernel;      /* the field advance in use: PIC2D_FIELD_TILES or _STRIPS */
   int32_t field_blocks;      /* its work-groups per launch */

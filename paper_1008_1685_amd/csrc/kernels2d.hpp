@@ -47,7 +47,7 @@ namespace pic {
 constexpr int k2SortBlock = PIC2D_SORT_BLOCK;  // log2 of the sort blocks' side in cells
 constexpr int k2Q = 12;                   // fixed-point bits of a shape weight
 constexpr int k2One = 1 << k2Q;
-constexpr int k2PPT = PIC2D_PUSH_PPT;     // particles per thread per tile
+constexpr int k2PPT = PIC2D_PUSH_PPT;     // particles per thread per tile (fewer in small runs)
 constexpr int k2Tile = kThreads * k2PPT;
 constexpr int k2Slots = PIC2D_LDS_SLOTS;  // 64-bit LDS accumulators per work-group
 #ifndef PIC2D_MAX_COPIES
@@ -599,7 +599,7 @@ __device__ __forceinline__ void push2_pass(const Push2Args<R>& a, const SpeciesD
   }
 }
 
-template <typename R, bool RR, bool COMP>
+template <typename R, bool RR, bool COMP, int PPT>
 __device__ __forceinline__ void push2_tile(const Push2Args<R>& a, int s, int tile, int n, int base,
                                            unsigned long long* lds, R* fst) {
   __shared__ int s_red[4][kThreads / kLanes];
@@ -609,9 +609,9 @@ __device__ __forceinline__ void push2_tile(const Push2Args<R>& a, int s, int til
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int ny = a.ny;
 
-  int cl[k2PPT];
+  int cl[PPT];
 #pragma unroll
-  for (int k = 0; k < k2PPT; ++k) {
+  for (int k = 0; k < PPT; ++k) {
     const int i = base + k * kThreads + tid;
     cl[k] = i < n ? ld(sp.cell, (unsigned)i) : kDead;
   }
@@ -622,7 +622,7 @@ __device__ __forceinline__ void push2_tile(const Push2Args<R>& a, int s, int til
   if (tid == 0) {
     int jr = 0;
 #pragma unroll
-    for (int k = k2PPT - 1; k >= 0; --k)
+    for (int k = PPT - 1; k >= 0; --k)
       if (cl[k] != kDead) jr = cl[k] & ((1 << a.ysh) - 1);
     s_jref = jr;
   }
@@ -630,13 +630,13 @@ __device__ __forceinline__ void push2_tile(const Push2Args<R>& a, int s, int til
   const int jref = __builtin_amdgcn_readfirstlane(s_jref);
   Range2 rg;
 #pragma unroll
-  for (int k = 0; k < k2PPT; ++k) rg.add(a, cl[k], jref);
+  for (int k = 0; k < PPT; ++k) rg.add(a, cl[k], jref);
   rg.reduce(s_red);
   if (rg.empty()) return;  // every particle of the tile was removed (block-uniform)
 
   Acc2 acc{0.f, 0.f, 0.f};
-  if (rg.slots(ny) <= k2Slots) {
-    push2_pass<R, RR, COMP, k2PPT>(a, sp, s, n, base, cl, first, rg, jref, lds, fst, acc);
+  if (PPT == 1 || rg.slots(ny) <= k2Slots) {
+    push2_pass<R, RR, COMP, PPT>(a, sp, s, n, base, cl, first, rg, jref, lds, fst, acc);
   } else {
     // The tile's box does not fit: its particles, in sort order, a
     // work-group's worth at a time, each with a box of its own.  Adding such
@@ -644,7 +644,7 @@ __device__ __forceinline__ void push2_tile(const Push2Args<R>& a, int s, int til
     // 83 of the 237 us of a push of 8.4e6 heated particles; it now takes 180
     // us (1.2e6 in FP64: 54, now 31).
 #pragma unroll 1
-    for (int k = 0; k < k2PPT; ++k) {
+    for (int k = 0; k < PPT; ++k) {
       const int i = base + k * kThreads + tid;
       const int one[1] = {i < n ? ld(sp.cell, (unsigned)i) : kDead};
       const P2<R> cur = load2<R, COMP>(sp, i, n, one[0]);
@@ -689,7 +689,7 @@ __device__ __forceinline__ void push2_tile(const Push2Args<R>& a, int s, int til
 #define PIC2D_PUSH_BOUNDS __launch_bounds__(kThreads)
 #endif
 
-template <typename R>
+template <typename R, int PPT>
 __global__ PIC2D_PUSH_BOUNDS void k_push2(Push2Args<R> a) {
   __shared__ unsigned long long lds[k2Slots];
   __shared__ R fst[6 * k2Stage];  // staged fields: E_z, B_z, (E_y, B_x), (E_x, B_y)
@@ -697,15 +697,15 @@ __global__ PIC2D_PUSH_BOUNDS void k_push2(Push2Args<R> a) {
   const int s = tile < a.tiles0 ? 0 : 1;
   const int tl = s ? tile - a.tiles0 : tile;
   const int n = (int)a.count[s];
-  const int base = tl * k2Tile;
+  const int base = tl * (kThreads * PPT);
   if (base >= n) return;
   if (s == 0 && a.rr0) {
     if (a.comp)
-      push2_tile<R, true, true>(a, s, tile, n, base, lds, fst);
+      push2_tile<R, true, true, PPT>(a, s, tile, n, base, lds, fst);
     else
-      push2_tile<R, true, false>(a, s, tile, n, base, lds, fst);
+      push2_tile<R, true, false, PPT>(a, s, tile, n, base, lds, fst);
   } else {
-    push2_tile<R, false, false>(a, s, tile, n, base, lds, fst);
+    push2_tile<R, false, false, PPT>(a, s, tile, n, base, lds, fst);
   }
 }
 

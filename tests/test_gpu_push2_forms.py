@@ -6,13 +6,14 @@ the contract's."""
 import numpy as np
 import pytest
 
-from test_gpu_pic2d import _contract_currents, _oracle, _setup, _zero_fields
+from test_gpu_pic2d import _contract_currents, _gpu_particles, _oracle, _zero_fields
 from workloads import preset2d, random_particles2d
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("tile,capacity", [(256, 0), (512, 1 << 18), (1024, 1 << 20)])
 @pytest.mark.parametrize("rows,group,patch,n", [
     (64, 256, (10, 10), 2348),   # patches of 256 particles: their tile's box does not fit
     (64, 256, (16, 48), 1024),   # patches near the largest box
@@ -20,8 +21,10 @@ pytestmark = pytest.mark.gpu
     (64, 1024, (12, 12), 2048),  # whole tiles that fit
     (5, 256, (4, 5), 1500),      # a period of 5 rows
 ])
-def test_push_boxes_bit_exact(precision, rows, group, patch, n):
-    print(f"\n[gpu] push2 {precision} {rows} rows, {group} per {patch}", flush=True)
+def test_push_boxes_bit_exact(precision, tile, capacity, rows, group, patch, n):
+    from paper_1008_1685_amd.run2d import Run2D
+
+    print(f"\n[gpu] push2 {precision} tile {tile}, {rows} rows, {group} per {patch}", flush=True)
     cfg = preset2d("d1", precision=precision, box_y=rows / 32, x_foil=1.0)
     sim = _oracle(cfg)
     nx, ny = sim.nx, sim.ny
@@ -35,7 +38,9 @@ def test_push_boxes_bit_exact(precision, rows, group, patch, n):
         p["ix"] = x0[g] + rng.integers(0, patch[0], n)
         p["iy"] = (y0[g] + rng.integers(0, patch[1], n)) % ny
         parts.append(p)
-    run = _setup(cfg, parts[0], parts[1], _zero_fields(nx, ny))
+    run = Run2D(cfg, capacity=max(n, capacity))
+    assert run.info["tile"] == tile
+    run.set_state({s: _gpu_particles(run, parts[s]) for s in (0, 1)}, fields=_zero_fields(nx, ny), step=0)
     run.push_deposit()
     st = run.get_state()
     J, moved = _contract_currents(cfg, sim, {0: parts[0], 1: parts[1]}, st, run)
