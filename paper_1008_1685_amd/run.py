@@ -165,7 +165,7 @@ class Run:
         if particles:
             for s in range(2):
                 cnt = st.sp[s].count
-                res[f"sp{s}"] = {k: a[:cnt].copy() for k, a in out[s].items()}
+                res[f"sp{s}"] = {k: a if cnt == len(a) else a[:cnt].copy() for k, a in out[s].items()}
         return res
 
     def get_particles(self, species: int, first: int, count: int, residuals: bool = False,

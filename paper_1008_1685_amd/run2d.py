@@ -156,7 +156,7 @@ class Run2D:
         if particles:
             for s in range(2):
                 cnt = st.sp[s].count
-                res[f"sp{s}"] = {k: a[:cnt].copy() for k, a in keep[s].items()}
+                res[f"sp{s}"] = {k: a if cnt == len(a) else a[:cnt].copy() for k, a in keep[s].items()}
         return res
 
     def set_state(self, particles: dict | None = None, fields: dict | None = None,
