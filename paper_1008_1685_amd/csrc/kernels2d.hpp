@@ -522,7 +522,11 @@ __device__ __forceinline__ void push2_pass(const Push2Args<R>& a, const SpeciesD
   }
   const int slots = rg.slots(ny);
   bx.CS = slots | 1;
-  int nc = k2MaxCopies;
+  // Copies spread the lanes' adds where neighbours share cells; 256 particles
+  // don't repay clearing and summing eight (128 steps of 16,384 particles:
+  // eight 2.34 ms, two 2.29; at four particles a thread two cost
+  // 12% and one 46% of 640 steps of 8.4e6 particles).
+  int nc = NK == 1 ? min(2, k2MaxCopies) : k2MaxCopies;
   while (nc > 1 && bx.CS * nc > k2Slots) nc >>= 1;
   bx.NC = nc;
   bx.use = bx.CS * nc <= k2Slots;
