@@ -1702,30 +1702,34 @@ struct TrackArgs {
 };
 
 // sin and cos of a phase: reduction by the nearest multiple of pi / 2 in
-// three parts (Cody and Waite) with fused multiply-adds, then the Taylor series
-// on [-pi/4, pi/4] up to the terms below half an ulp (r^15 and r^16).  About 35
-// instructions; the library's sincos carries the reduced argument in two parts
-// and branches for huge ones, about 75, of the 285 of a step of a tracked
-// electron whose serial chain is the launch's time.  Phases past 1e5, where
-// the three parts would not suffice, and non-finite ones go to the library.
+// three parts (Cody and Waite) with fused multiply-adds, the reduced argument
+// kept with its rounding error, then the Taylor series on [-pi/4, pi/4] up to
+// the terms below a twentieth of an ulp (r^17 and r^16).  At most 0.8 ulp off
+// for phases below 1e5 (1.5 without the kept error and the last term).  About
+// 40 instructions; the library's sincos takes about 75, of the 285 of a step
+// of a tracked electron whose serial chain is the launch's time.  Phases past
+// 1e5, where the three parts would not suffice, and non-finite ones go to the
+// library.
 __device__ __forceinline__ void phase_sincos(double x, double* sn, double* cs) {
   if (!(fabs(x) < 1e5)) {
     sincos(x, sn, cs);
     return;
   }
   const double n = rint(x * 0x1.45f306dc9c883p-1);  // 2 / pi
-  double r = fma(-n, 0x1.921fb54442d18p+0, x);
-  r = fma(-n, 0x1.1a62633145c07p-54, r);
-  r = fma(-n, -0x1.f1976b7ed8fbcp-110, r);
+  const double t = fma(-n, 0x1.921fb54442d18p+0, x);  // exact
+  const double r = fma(-n, 0x1.1a62633145c07p-54, t);
+  const double lo = fma(-n, -0x1.f1976b7ed8fbcp-110, fma(-n, 0x1.1a62633145c07p-54, t - r));
   const double z = r * r;
-  double p = -1.0 / 1307674368000.0;
+  double p = 1.0 / 355687428096000.0;
+  p = fma(p, z, -1.0 / 1307674368000.0);
   p = fma(p, z, 1.0 / 6227020800.0);
   p = fma(p, z, -1.0 / 39916800.0);
   p = fma(p, z, 1.0 / 362880.0);
   p = fma(p, z, -1.0 / 5040.0);
   p = fma(p, z, 1.0 / 120.0);
   p = fma(p, z, -1.0 / 6.0);
-  const double s = fma(z * r, p, r);
+  const double hz = 0.5 * z;
+  const double s = r + fma(z * r, p, fma(-hz, lo, lo));  // sin r + lo cos r
   double q = 1.0 / 20922789888000.0;
   q = fma(q, z, -1.0 / 87178291200.0);
   q = fma(q, z, 1.0 / 479001600.0);
@@ -1734,8 +1738,8 @@ __device__ __forceinline__ void phase_sincos(double x, double* sn, double* cs) {
   q = fma(q, z, -1.0 / 720.0);
   q = fma(q, z, 1.0 / 24.0);
   // 1 - z / 2 in two parts, so that its rounding does not enter
-  const double hz = 0.5 * z, w = 1.0 - hz;
-  const double c = w + fma(z * z, q, (1.0 - w) - hz);
+  const double w = 1.0 - hz;
+  const double c = w + fma(z * z, q, fma(-r, lo, (1.0 - w) - hz));
   const int k = (int)n;
   const double a = k & 1 ? c : s, b = k & 1 ? s : c;
   *sn = k & 2 ? -a : a;
