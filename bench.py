@@ -394,8 +394,8 @@ def serve_bench(n_runs=256, rate=20.0, seed=0, max_slots=64, budget_gb=64.0, per
     """Serving form: a Poisson stream of independent laser-foil requests
     (a0, polarisation, density, thickness, size and length randomised),
     continuously batched; latency = completion - arrival.  persistent: each
-    quantum's steps as one persistent launch rather than a push and a field
-    launch per step; groups: the slots split over that many batches on
+    quantum's steps as one persistent launch rather than one fused launch
+    per step; groups: the slots split over that many batches on
     streams of their own; saturated: every request queued at time 0 (the
     batch's throughput with no idle slot, rather than the stream's latency)."""
     import numpy as np
@@ -431,7 +431,7 @@ def serve_bench(n_runs=256, rate=20.0, seed=0, max_slots=64, budget_gb=64.0, per
                 peak_resident_bytes=srv.peak_bytes, max_slots=max_slots, groups=len(srv.batches),
                 failed_checks=bad,
                 launch_form="one persistent launch per quantum" if persistent
-                else "a push and a field launch per step")
+                else "one launch per step: fields and the next push")
 
 
 def stress_bench(serve_kwargs, t_start=8.5, window=200, chunk=8, max_grid=512):
@@ -681,7 +681,7 @@ def main():
     if not args.no_serve:
         line["serving"] = serve_bench()
         # the same stream with each quantum's steps in one persistent launch
-        # (measured slower; the default keeps a push and a field launch per step)
+        # (measured slower; the default keeps one launch per step)
         per = serve_bench(persistent=True, groups=1)
         line["serving_persistent_form"] = {k: per[k] for k in ("p50_s", "p99_s", "mean_s", "wall_s",
                                                                "pushes_per_s", "failed_checks",
