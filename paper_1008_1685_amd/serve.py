@@ -71,7 +71,7 @@ class Batch:
 
     def set_persistent(self, on):
         """Launch each quantum's steps as one persistent launch (True) or as
-        one push and one field launch per step (False, the default); 2 is the
+        one launch per step, fields and the next push (False, the default); 2 is the
         persistent form with its barrier waits cut to zero (the error path)."""
         mode = on if isinstance(on, int) and not isinstance(on, bool) else (1 if on else 0)
         N.check(self.lib.pic_batch_set_persistent(self._h, mode), "pic_batch_set_persistent")
