@@ -1341,14 +1341,14 @@ pic_status pic_set_state(pic_run* r, const pic_state* st, void* stream) {
       HIP_TRY(hipMemcpy(r->FH[pn], r->FH[po], (size_t)(d.nx + 2) * 4 * rs, hipMemcpyDeviceToDevice));
       HIP_TRY(hipMemcpy(r->Ex_int[pn], r->Ex_int[po], (d.nx + 2) * sizeof(long long), hipMemcpyDeviceToDevice));
     }
-    // the current of the step in progress moves with it, the others are clear
+    // the current of the step in progress moves with it, the others are
+    // cleared: the last step's is still in its buffer, and a run set back to
+    // step 0 may join a batch, which takes the buffers in another order
     const int jo = j_index(r, r->step), jn = j_index(r, st->step);
-    if (jo != jn) {
-      const size_t jb = 3 * r->jstride * sizeof(unsigned long long);
-      HIP_TRY(hipMemcpy(j_buf(r, jn, 0), j_buf(r, jo, 0), jb, hipMemcpyDeviceToDevice));
-      for (int b = 0; b < 3; ++b)
-        if (b != jn) HIP_TRY(hipMemset(j_buf(r, b, 0), 0, jb));
-    }
+    const size_t jb = 3 * r->jstride * sizeof(unsigned long long);
+    if (jo != jn) HIP_TRY(hipMemcpy(j_buf(r, jn, 0), j_buf(r, jo, 0), jb, hipMemcpyDeviceToDevice));
+    for (int b = 0; b < 3; ++b)
+      if (b != jn) HIP_TRY(hipMemset(j_buf(r, b, 0), 0, jb));
     r->step = st->step;
     const long long both[2] = {r->step, r->step};
     HIP_TRY(hipMemcpy(r->step_dev, both, sizeof(both), hipMemcpyHostToDevice));
