@@ -241,6 +241,9 @@ pic_status pic_sort(struct pic_run* run, void* stream);
  * (pic_get_info); removed particles are skipped, so counts are alive counts
  * (all particle arrays NULL: fields and currents only, count set to 0).
  * pic_get_state always fills `budget` (valid = 1).
+ * A read changes nothing a step reads or writes (the grids pass through
+ * memory of the workspace that only state I/O uses); it waits for `stream`,
+ * so steps in flight on another stream give a mixture of states.
  * pic_set_state validates cells and offsets, replaces the particle arrays
  * (count <= capacity; the current buffers of both parities are cleared when
  * particles are replaced) and/or fields, Ex_int and the current buffers of

@@ -175,7 +175,8 @@ pic_status pic2d_get_info(const struct pic2d_run* run, pic2d_info* out);
 void pic2d_free(struct pic2d_run* run);
 
 /* State I/O (host buffers), blocking.  get: particle arrays hold `capacity`
- * entries, removed particles are skipped; any pointer may be NULL.  set:
+ * entries, removed particles are skipped; any pointer may be NULL; the run
+ * is left as it is, as by pic_get_state.  set:
  * validates cells and offsets; replacing particles clears both current
  * buffers and restarts charge_int from the new particles' charge; fields,
  * currents and charge_int are written when given; step >= 0 resets the

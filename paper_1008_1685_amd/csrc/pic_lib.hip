@@ -130,7 +130,7 @@ struct TimingRec {
 }  // namespace
 
 struct pic_run {
-  std::mutex io;        // state I/O of one run takes turns: it shares the other parity's fields
+  std::mutex io;        // state I/O of one run takes turns: it shares io_grid
   pic_config cfg;
   Derived d;
   long long n_max[2];   // host upper bound of particles per species
@@ -162,6 +162,7 @@ struct pic_run {
   long long* ipart;
   DiagOutDev* dout;
   unsigned long long* hist;
+  void* io_grid;        // state I/O: one component of the fields
   int tiles_max;
   int push_tile = kTile;  // particles per push work-group: kTile, or small_tile()
   struct pic_batch* batch = nullptr;  // set while the run is stepped by a batch
@@ -233,6 +234,7 @@ void carve(pic_run* r, Carver& cv) {
   r->ipart = cv.take<long long>(kDiagFieldBlocks + 2 * kDiagPartBlocks);
   r->dout = cv.take<DiagOutDev>(1);
   r->hist = cv.take<unsigned long long>(kMaxSpectrumBins);
+  r->io_grid = cv.take<char>((size_t)(d.nx + 2) * rs);
 }
 
 template <typename R>
@@ -993,53 +995,57 @@ __global__ void k_put(const T* src, T* dst, long long n, int stride, int member)
 
 // Component `member` of n values of rs bytes, stride apart, between a host
 // array and the device.  The (de)interleaving runs on the device through
-// `scratch` (n values: the buffer of the other step parity, which the next
-// field pass rewrites), so that only what was asked for crosses to the host,
-// once, into the caller's own array.  Blocking.  The interleaved array
+// `scratch` (n values of the workspace that nothing else uses: a read may not
+// touch what a step reads or writes), so that only what was asked for crosses
+// to the host, once, into the caller's own array.  On the null stream, as the
+// blocking copies of the other arrays.  Blocking.  The interleaved array
 // through a host copy entry by entry, and the particles likewise, cost 6.0 ms
 // for a save and restore (12,000 cells, 200,000 particles a species, FP32),
 // this way 2.1 ms; 11 ms of the reads of a 2,560 x 1,024 run's grids went.
 pic_status component_to_host(void* host, const void* base, void* scratch, long long n, int stride, int member,
-                             size_t rs, hipStream_t s) {
+                             size_t rs) {
   const void* from = base;
   if (stride > 1) {
     const dim3 grid((unsigned)((n + 255) / 256));
     if (rs == 4)
-      hipLaunchKernelGGL(k_take<float>, grid, dim3(256), 0, s, (const float*)base, (float*)scratch, n, stride, member);
+      hipLaunchKernelGGL(k_take<float>, grid, dim3(256), 0, nullptr, (const float*)base, (float*)scratch, n, stride,
+                         member);
     else
-      hipLaunchKernelGGL(k_take<double>, grid, dim3(256), 0, s, (const double*)base, (double*)scratch, n, stride, member);
+      hipLaunchKernelGGL(k_take<double>, grid, dim3(256), 0, nullptr, (const double*)base, (double*)scratch, n,
+                         stride, member);
     HIP_TRY(hipGetLastError());
     from = scratch;
   }
-  HIP_TRY(hipMemcpyAsync(host, from, n * rs, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(hipMemcpy(host, from, n * rs, hipMemcpyDeviceToHost));
   return PIC_OK;
 }
 pic_status component_to_device(void* base, void* scratch, const void* host, long long n, int stride, int member,
-                               size_t rs, hipStream_t s) {
-  HIP_TRY(hipMemcpyAsync(stride > 1 ? scratch : base, host, n * rs, hipMemcpyHostToDevice, s));
+                               size_t rs) {
+  HIP_TRY(hipMemcpy(stride > 1 ? scratch : base, host, n * rs, hipMemcpyHostToDevice));
   if (stride > 1) {
     const dim3 grid((unsigned)((n + 255) / 256));
     if (rs == 4)
-      hipLaunchKernelGGL(k_put<float>, grid, dim3(256), 0, s, (const float*)scratch, (float*)base, n, stride, member);
+      hipLaunchKernelGGL(k_put<float>, grid, dim3(256), 0, nullptr, (const float*)scratch, (float*)base, n, stride,
+                         member);
     else
-      hipLaunchKernelGGL(k_put<double>, grid, dim3(256), 0, s, (const double*)scratch, (double*)base, n, stride, member);
+      hipLaunchKernelGGL(k_put<double>, grid, dim3(256), 0, nullptr, (const double*)scratch, (double*)base, n,
+                         stride, member);
     HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(nullptr));
   }
-  HIP_TRY(hipStreamSynchronize(s));
   return PIC_OK;
 }
 
 // Component k (0 Ex, 1 Ey, 2 Ez, 3 By, 4 Bz) of a run's current fields.
 struct Comp1 {
-  void *base, *scratch;
+  void* base;
   long long len;
   int stride, member;
 };
 Comp1 comp1(const pic_run* r, int k) {
   const int p = (int)(r->step & 1);
-  if (k == 1 || k == 2) return {r->FN[p], r->FN[p ^ 1], r->d.nx + 1, 2, k - 1};
-  return {r->FH[p], r->FH[p ^ 1], r->d.nx + 2, 4, k == 0 ? 0 : k - 2};
+  if (k == 1 || k == 2) return {r->FN[p], r->d.nx + 1, 2, k - 1};
+  return {r->FH[p], r->d.nx + 2, 4, k == 0 ? 0 : k - 2};
 }
 
 // One particle array of n entries to the host: as it is when every particle
@@ -1299,7 +1305,7 @@ pic_status pic_get_state(pic_run* r, pic_state* st, void* stream) {
     for (int k = 0; k < 5; ++k) {
       if (!outs[k]) continue;
       const Comp1 c = comp1(r, k);
-      pic_status ps = component_to_host(outs[k], c.base, c.scratch, c.len, c.stride, c.member, rs, s);
+      pic_status ps = component_to_host(outs[k], c.base, r->io_grid, c.len, c.stride, c.member, rs);
       if (ps) return ps;
     }
   }
@@ -1402,7 +1408,7 @@ pic_status pic_set_state(pic_run* r, const pic_state* st, void* stream) {
     for (int k = 0; k < 5; ++k) {
       if (!ins[k]) continue;
       const Comp1 c = comp1(r, k);
-      pic_status ps = component_to_device(c.base, c.scratch, ins[k], c.len, c.stride, c.member, rs, s);
+      pic_status ps = component_to_device(c.base, r->io_grid, ins[k], c.len, c.stride, c.member, rs);
       if (ps) return ps;
     }
   }

@@ -4,7 +4,7 @@ stream too, and a read changes nothing that a step in flight could touch."""
 import numpy as np
 import pytest
 
-from workloads import preset2d
+from workloads import preset, preset2d
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +44,42 @@ def test_push_follows_the_cleared_currents_2d(what, precision):
         if "fields" in what or k[0] in "Jc":
             assert np.array_equal(sa[k], sb[k]), k
     assert np.any(sa["Jx_int"])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("before", [0, 1])
+@pytest.mark.parametrize("dims", [1, 2])
+def test_reads_write_scratch_only(dims, before, precision):
+    import torch
+
+    from paper_1008_1685_amd import Run
+    from paper_1008_1685_amd.run2d import Run2D
+
+    print(f"\n[gpu] reads {dims}D {before} {precision}", flush=True)
+    if dims == 1:
+        run = Run(preset("c1", precision=precision))
+        scratch = (run.info["n_cells"] + 2) * np.dtype(run.rdt).itemsize
+    else:
+        run = Run2D(preset2d("d1", precision=precision, box_x=3.0, box_y=1.91, x_foil=1.0, thickness=0.5))
+        scratch = (run.info["nx"] + 2) * run.info["ny"] * np.dtype(run.rdt).itemsize
+    rng = np.random.default_rng(before)
+    run.step(before)
+    st = run.get_state(particles=False)
+    run.set_state(fields={k: rng.uniform(-5, 5, v.shape) for k, v in st.items()
+                          if isinstance(v, np.ndarray) and k[0] in "EB" and not k.endswith("_int")})
+    run.step(3)  # (both parities of the fields hold values of their own)
+    torch.cuda.synchronize()
+    old = run.ws.clone()
+    run.get_state()
+    run.get_state(particles=False)
+    at = torch.nonzero(run.ws[: run.ws_bytes] != old[: run.ws_bytes]).flatten()
+    # nothing but one component's worth of scratch, outside every array of the run
+    assert at.numel() == 0 or int(at[-1] - at[0]) < scratch, (int(at[0]), int(at[-1]), scratch)
+    run.step(1)
+    torch.cuda.synchronize()
+    new = run.ws.clone()
+    if at.numel():
+        lo, hi = int(at[0]), int(at[-1]) + 1
+        run.step(4)
+        torch.cuda.synchronize()
+        assert torch.equal(run.ws[lo:hi], new[lo:hi])
