@@ -993,6 +993,19 @@ __global__ void k_put(const T* src, T* dst, long long n, int stride, int member)
   if (i < n) dst[i * stride + member] = src[i];
 }
 
+// A launch that reports its own error.  hipGetLastError would also report
+// what another call of this thread left behind, for which state I/O is not
+// refused: it checks its copies by their own status too.
+template <typename T>
+struct Same {
+  using type = T;
+};
+template <typename... P>
+hipError_t launch_own(void (*k)(P...), dim3 grid, dim3 block, hipStream_t st, typename Same<P>::type... args) {
+  void* at[] = {const_cast<void*>(static_cast<const void*>(&args))...};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k), grid, block, at, 0, st);
+}
+
 // Component `member` of n values of rs bytes, stride apart, between a host
 // array and the device.  The (de)interleaving runs on the device through
 // `scratch` (n values of the workspace that nothing else uses: a read may not
@@ -1006,14 +1019,11 @@ pic_status component_to_host(void* host, const void* base, void* scratch, long l
                              size_t rs) {
   const void* from = base;
   if (stride > 1) {
-    const dim3 grid((unsigned)((n + 255) / 256));
-    if (rs == 4)
-      hipLaunchKernelGGL(k_take<float>, grid, dim3(256), 0, nullptr, (const float*)base, (float*)scratch, n, stride,
-                         member);
-    else
-      hipLaunchKernelGGL(k_take<double>, grid, dim3(256), 0, nullptr, (const double*)base, (double*)scratch, n,
-                         stride, member);
-    HIP_TRY(hipGetLastError());
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    HIP_TRY(rs == 4 ? launch_own(k_take<float>, grid, block, nullptr, (const float*)base, (float*)scratch, n, stride,
+                                 member)
+                    : launch_own(k_take<double>, grid, block, nullptr, (const double*)base, (double*)scratch, n,
+                                 stride, member));
     from = scratch;
   }
   HIP_TRY(hipMemcpy(host, from, n * rs, hipMemcpyDeviceToHost));
@@ -1023,14 +1033,11 @@ pic_status component_to_device(void* base, void* scratch, const void* host, long
                                size_t rs) {
   HIP_TRY(hipMemcpy(stride > 1 ? scratch : base, host, n * rs, hipMemcpyHostToDevice));
   if (stride > 1) {
-    const dim3 grid((unsigned)((n + 255) / 256));
-    if (rs == 4)
-      hipLaunchKernelGGL(k_put<float>, grid, dim3(256), 0, nullptr, (const float*)scratch, (float*)base, n, stride,
-                         member);
-    else
-      hipLaunchKernelGGL(k_put<double>, grid, dim3(256), 0, nullptr, (const double*)scratch, (double*)base, n,
-                         stride, member);
-    HIP_TRY(hipGetLastError());
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    HIP_TRY(rs == 4 ? launch_own(k_put<float>, grid, block, nullptr, (const float*)scratch, (float*)base, n, stride,
+                                 member)
+                    : launch_own(k_put<double>, grid, block, nullptr, (const double*)scratch, (double*)base, n,
+                                 stride, member));
     HIP_TRY(hipStreamSynchronize(nullptr));
   }
   return PIC_OK;
@@ -1358,11 +1365,9 @@ pic_status pic_set_state(pic_run* r, const pic_state* st, void* stream) {
     r->step = st->step;
     const long long both[2] = {r->step, r->step};
     HIP_TRY(hipMemcpy(r->step_dev, both, sizeof(both), hipMemcpyHostToDevice));
-    if (d.prec == PIC_FP32)
-      hipLaunchKernelGGL(k_incident<float>, dim3(1), dim3(1), 0, s, make_field_args<float>(r, 0, false), r->step);
-    else
-      hipLaunchKernelGGL(k_incident<double>, dim3(1), dim3(1), 0, s, make_field_args<double>(r, 0, false), r->step);
-    HIP_TRY(hipGetLastError());
+    HIP_TRY(d.prec == PIC_FP32
+                ? launch_own(k_incident<float>, dim3(1), dim3(1), s, make_field_args<float>(r, 0, false), r->step)
+                : launch_own(k_incident<double>, dim3(1), dim3(1), s, make_field_args<double>(r, 0, false), r->step));
   }
   for (int sp = 0; sp < 2; ++sp) {
     const pic_species_state& o = st->sp[sp];
