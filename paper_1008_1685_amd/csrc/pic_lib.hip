@@ -158,6 +158,7 @@ struct pic_run {
   int* cnt[2];
   int* cursor[2];
   long long* rho;
+  bool rho_open = false;  // a diagnostics call may have left charge in rho
   double* part;
   long long* ipart;
   DiagOutDev* dout;
@@ -668,6 +669,22 @@ void finish_balance(pic_diag_out* o) {
                o->E_in;
 }
 
+__global__ void k_fill_u64(unsigned long long* p, int n, unsigned long long v) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < n) p[i] = v;
+}
+
+// The charge array of a run (n nodes) is zero between diagnostics calls: each
+// call's field pass clears what its particle pass added.  A call that failed
+// in between left it as it may be, and the next one starts by clearing it.
+template <typename Run>
+void begin_charge(Run* r, long long n, hipStream_t st) {
+  if (r->rho_open)
+    hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                       (unsigned long long*)r->rho, (int)n, 0ull);
+  r->rho_open = true;
+}
+
 template <typename R>
 pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   const Derived& d = r->d;
@@ -688,11 +705,13 @@ pic_status do_diag(pic_run* r, pic_diag_out* out, hipStream_t st) {
   p.Z[1] = 1;
   p.sw = (R)(256.0 / d.w_ref);
   p.dx = d.dx;
+  begin_charge(r, d.nx + 3, st);
   hipLaunchKernelGGL(k_diag_particles<R>, dim3(2 * kDiagPartBlocks), dim3(kDiagThreads), 0, st, p);
   hipLaunchKernelGGL(k_diag_fields<R>, dim3(kDiagFieldBlocks), dim3(kDiagThreads), 0, st, p);
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagThreads), 0, st, r->part, r->ipart, r->budget,
                      r->flags, r->step_dev + (r->step & 1), r->dout);
   HIP_TRY(hipGetLastError());
+  r->rho_open = false;
   DiagOutDev o;
   HIP_TRY(hipMemcpyAsync(&o, r->dout, sizeof(o), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -954,11 +973,6 @@ dim3 hist_grid(long long n) {
 }
 
 // ---------------------------------------------------------------- static scratch
-__global__ void k_fill_u64(unsigned long long* p, int n, unsigned long long v) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i < n) p[i] = v;
-}
-
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 unsigned long long* g_scratch_ptr[kMaxDevices] = {};

@@ -64,3 +64,22 @@ def test_state_calls_go_through(dims, precision):
     assert got["step"] == 100
     for k in fields:
         assert np.array_equal(fields[k], got[k]), k
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("dims", [1, 2])
+def test_diagnostics_after_a_failed_call(dims, precision):
+    from paper_1008_1685_amd import PicError
+
+    print(f"\n[gpu] pending error, diag {dims}D {precision}", flush=True)
+    run = _run(dims, precision)
+    run.step(3)
+    want = run.diag()
+    assert want["gauss_int"] == 0
+    with _Pending():
+        try:
+            run.diag()
+        except PicError:
+            pass
+    for _ in range(2):
+        assert run.diag() == want
