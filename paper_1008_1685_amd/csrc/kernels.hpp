@@ -177,6 +177,13 @@ __device__ __forceinline__ double rcp(double x) { return rcp_rn_ge1(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double fsqrt(double x) { return sqrt_rn_ge1(x); }
 
+// The same where a square may overflow without the particle being dropped (a
+// tracked electron has the momentum its caller gave it): infinity gives 0.
+__device__ __forceinline__ float rsq_any(float x) { return rsq(x); }
+__device__ __forceinline__ double rsq_any(double x) { return x == INFINITY ? 0.0 : rsq(x); }
+__device__ __forceinline__ float rcp_any(float x) { return rcp(x); }
+__device__ __forceinline__ double rcp_any(double x) { return x == INFINITY ? 0.0 : rcp(x); }
+
 // Element i of an array at a wave-uniform base: a 32-bit byte offset added
 // to the 64-bit base lets the compiler use scalar-base addressing instead of
 // per-lane 64-bit address arithmetic.  Arrays stay below 4 GiB (capacity
@@ -477,8 +484,9 @@ struct MomentumOut {
 // in (rx, ry, rz).  DERIV adds the derivative term of Eq. (3dLL) at the same
 // p^(n) (the complete LL force, for tracking in given fields).  BX takes a
 // non-zero B_x (multi-dimensional grids); without it B_x = 0, as in 1D, and
-// none of its terms is evaluated.
-template <typename R, bool RR, bool COMP, bool DERIV, bool BX = false>
+// none of its terms is evaluated.  ANY: momenta whose square overflows are
+// stepped too (the runs drop them after the step).
+template <typename R, bool RR, bool COMP, bool DERIV, bool BX = false, bool ANY = false>
 __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez, R by, R bz, R qh,
                                               R k, const FieldRates<R>& fr, float& rx, float& ry,
                                               float& rz, float& stiff, MomentumOut<R>& o,
@@ -486,7 +494,8 @@ __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez
   // Boris
   const R hx = qh * ex, hy = qh * ey, hz = qh * ez;
   const R mx = ux + hx, my = uy + hy, mz = uz + hz;
-  const R igm = rsq(R(1) + mx * mx + my * my + mz * mz);
+  const R m2 = R(1) + mx * mx + my * my + mz * mz;
+  const R igm = ANY ? rsq_any(m2) : rsq(m2);
   const R ty = qh * by * igm, tz = qh * bz * igm;
   R tx = R(0), den;
   if constexpr (BX) {
@@ -495,7 +504,7 @@ __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez
   } else {
     den = R(1) + ty * ty + tz * tz;
   }
-  const R sf = R(2) * rcp(den);
+  const R sf = R(2) * (ANY ? rcp_any(den) : rcp(den));
   R px = mx + (my * tz - mz * ty);
   R py = my - mx * tz;
   R pz = mz + mx * ty;
@@ -519,7 +528,7 @@ __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez
     // mid-step momentum (u_L + u^{n-1/2}) / 2 and its velocity
     const R qx = R(0.5) * (Lx + ux), qy = R(0.5) * (Ly + uy), qz = R(0.5) * (Lz + uz);
     const R g2 = R(1) + qx * qx + qy * qy + qz * qz;
-    const R ig = rsq(g2);
+    const R ig = ANY ? rsq_any(g2) : rsq(g2);
     const R vx = qx * ig, vy = qy * ig, vz = qz * ig;
     // F = E + v x B = -f_L
     const R Fx = ex + (vy * bz - vz * by);
@@ -1768,48 +1777,75 @@ __device__ __forceinline__ void wave_at(const TrackArgs& a, double x, double t, 
   fr.bxz = -dy;
 }
 
+// A tracked electron; FP32 carries the RR increment's rounding residual.
+template <typename R>
+struct TrackState {
+  double x;
+  R ux, uy, uz;
+  float rx, ry, rz;
+};
+
+// Whether an electron's squared momentum may overflow FP64 before its last
+// step.  From a moderate momentum only the RR force gets there, and the step
+// after is not finite in any form; so ANY (selects on the chain of every step:
+// 1.16 ms become 1.29 for 10,000 electrons and 2,000 steps, a check after each
+// step 1.24) is for the last step and for electrons that begin so (1.18).
+template <typename R>
+__device__ __forceinline__ bool may_overflow(const TrackArgs& a, const TrackState<R>& e) {
+  const double kick = (fabs(a.ay) + fabs(a.az)) * fmax(1.0, fabs(a.dt));
+  return sizeof(R) == 8 && !(fabs(e.ux) + fabs(e.uy) + fabs(e.uz) < 1e140 && kick < 1e100);
+}
+
 // The paper's leapfrog scheme: x^n and u^{n-1/2} in, x^{n+steps} and
 // u^{n+steps-1/2} out; the position advances in FP64 by dt u_x / gamma.
 // MODE: 0 Lorentz only, 1 with f_R of Eq. (f_r), 2 with the complete force.
+template <typename R, int MODE, bool ANY>
+__device__ __forceinline__ void leapfrog_step(const TrackArgs& a, double t, R qh, R k, TrackState<R>& e) {
+  constexpr bool COMP = sizeof(R) == 4 && MODE > 0;
+  float stiff = 0.f;
+  R ey, ez;
+  FieldRates<R> fr;
+  wave_at<R>(a, e.x, t, ey, ez, fr);
+  MomentumOut<R> o;
+  momentum_step<R, (MODE > 0), COMP, (MODE == 2), false, ANY>(e.ux, e.uy, e.uz, R(0), ey, ez, -ez, ey, qh, k, fr,
+                                                              e.rx, e.ry, e.rz, stiff, o);
+  e.ux = o.nx;
+  e.uy = o.ny;
+  e.uz = o.nz;
+  const double gx = (double)e.ux + e.rx, gy = (double)e.uy + e.ry, gz = (double)e.uz + e.rz;
+  const double g2 = 1.0 + gx * gx + gy * gy + gz * gz;
+  e.x += a.dt * gx * (ANY ? rsq_any(g2) : rsq(g2));
+}
+
 template <typename R, int MODE>
 __global__ void k_track_leapfrog(TrackArgs a) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  constexpr bool COMP = sizeof(R) == 4 && MODE > 0;
-  double x = a.x[i];
-  R ux = (R)a.ux[i], uy = (R)a.uy[i], uz = (R)a.uz[i];
-  float rx = 0.f, ry = 0.f, rz = 0.f, stiff = 0.f;
+  TrackState<R> e{a.x[i], (R)a.ux[i], (R)a.uy[i], (R)a.uz[i], 0.f, 0.f, 0.f};
   const R qh = (R)(-0.5 * a.dt), k = (R)(a.eps * a.dt);
-  for (long long s = 0; s < a.steps; ++s) {
-    R ey, ez;
-    FieldRates<R> fr;
-    wave_at<R>(a, x, a.t0 + (double)s * a.dt, ey, ez, fr);
-    MomentumOut<R> o;
-    momentum_step<R, (MODE > 0), COMP, (MODE == 2)>(ux, uy, uz, R(0), ey, ez, -ez, ey, qh, k, fr, rx,
-                                                    ry, rz, stiff, o);
-    ux = o.nx;
-    uy = o.ny;
-    uz = o.nz;
-    const double gx = (double)ux + rx, gy = (double)uy + ry, gz = (double)uz + rz;
-    x += a.dt * gx * rcp_rn_ge1(sqrt_rn_ge1(1.0 + gx * gx + gy * gy + gz * gz));
-  }
-  a.x[i] = x;
-  a.ux[i] = (double)ux + rx;
-  a.uy[i] = (double)uy + ry;
-  a.uz[i] = (double)uz + rz;
+  long long s = 0;
+  if (!may_overflow(a, e))
+    for (; s < a.steps - 1; ++s) leapfrog_step<R, MODE, false>(a, a.t0 + (double)s * a.dt, qh, k, e);
+  for (; s < a.steps; ++s) leapfrog_step<R, MODE, true>(a, a.t0 + (double)s * a.dt, qh, k, e);
+  a.x[i] = e.x;
+  a.ux[i] = (double)e.ux + e.rx;
+  a.uy[i] = (double)e.uy + e.ry;
+  a.uz[i] = (double)e.uz + e.rz;
 }
 
+template <bool ANY>
 __device__ __forceinline__ float inv_gamma(float g2) { return 1.0f / sqrtf(g2); }
-__device__ __forceinline__ double inv_gamma(double g2) { return rsq(g2); }
+template <bool ANY>
+__device__ __forceinline__ double inv_gamma(double g2) { return ANY ? rsq_any(g2) : rsq(g2); }
 
 // Right-hand side of Eq. (3dLL) for an electron (MODE 0: Lorentz only; 1:
 // plus the non-derivative RR terms; 2: plus the derivative term).
-template <typename R, int MODE>
+template <typename R, int MODE, bool ANY>
 __device__ __forceinline__ void ll_rhs(R ux, R uy, R uz, R ey, R ez, const FieldRates<R>& fr, R eps,
                                        R& fx, R& fy, R& fz) {
   const R by = -ez, bz = ey;
   const R g2 = R(1) + ux * ux + uy * uy + uz * uz;
-  const R ig = inv_gamma(g2);
+  const R ig = inv_gamma<ANY>(g2);
   const R vx = ux * ig, vy = uy * ig, vz = uz * ig;
   const R Fx = vy * bz - vz * by, Fy = ey - vx * bz, Fz = ez + vx * by;  // E + v x B (E_x = 0)
   fx = -Fx;
@@ -1833,39 +1869,45 @@ __device__ __forceinline__ void ll_rhs(R ux, R uy, R uz, R ey, R ez, const Field
 }
 
 // Classical RK4 of (x, u) at the same time, the comparator of Section 3.
-template <typename R, int MODE>
-__global__ void k_track_rk4(TrackArgs a) {
-  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
-  double x = a.x[i];
-  R ux = (R)a.ux[i], uy = (R)a.uy[i], uz = (R)a.uz[i];
-  const R h = (R)a.dt, eps = (R)a.eps;
+template <typename R, int MODE, bool ANY>
+__device__ __forceinline__ void rk4_step(const TrackArgs& a, double t, R h, R eps, TrackState<R>& e) {
   auto stage = [&](double xs, double ts, R sx, R sy, R sz, double& dx, R& fx, R& fy, R& fz) {
     R ey, ez;
     FieldRates<R> fr;
     wave_at<R>(a, xs, ts, ey, ez, fr);
-    ll_rhs<R, MODE>(sx, sy, sz, ey, ez, fr, eps, fx, fy, fz);
-    dx = (double)sx * rsq(1.0 + (double)sx * sx + (double)sy * sy + (double)sz * sz);
+    ll_rhs<R, MODE, ANY>(sx, sy, sz, ey, ez, fr, eps, fx, fy, fz);
+    dx = (double)sx * inv_gamma<ANY>(1.0 + (double)sx * sx + (double)sy * sy + (double)sz * sz);
   };
-  for (long long s = 0; s < a.steps; ++s) {
-    const double t = a.t0 + (double)s * a.dt;
-    double d1, d2, d3, d4;
-    R a1, b1, c1, a2, b2, c2, a3, b3, c3, a4, b4, c4;
-    stage(x, t, ux, uy, uz, d1, a1, b1, c1);
-    stage(x + 0.5 * a.dt * d1, t + 0.5 * a.dt, ux + R(0.5) * h * a1, uy + R(0.5) * h * b1,
-          uz + R(0.5) * h * c1, d2, a2, b2, c2);
-    stage(x + 0.5 * a.dt * d2, t + 0.5 * a.dt, ux + R(0.5) * h * a2, uy + R(0.5) * h * b2,
-          uz + R(0.5) * h * c2, d3, a3, b3, c3);
-    stage(x + a.dt * d3, t + a.dt, ux + h * a3, uy + h * b3, uz + h * c3, d4, a4, b4, c4);
-    x += a.dt / 6.0 * (d1 + 2.0 * d2 + 2.0 * d3 + d4);
-    ux += h / R(6) * (a1 + R(2) * a2 + R(2) * a3 + a4);
-    uy += h / R(6) * (b1 + R(2) * b2 + R(2) * b3 + b4);
-    uz += h / R(6) * (c1 + R(2) * c2 + R(2) * c3 + c4);
-  }
-  a.x[i] = x;
-  a.ux[i] = ux;
-  a.uy[i] = uy;
-  a.uz[i] = uz;
+  const double x = e.x;
+  const R ux = e.ux, uy = e.uy, uz = e.uz;
+  double d1, d2, d3, d4;
+  R a1, b1, c1, a2, b2, c2, a3, b3, c3, a4, b4, c4;
+  stage(x, t, ux, uy, uz, d1, a1, b1, c1);
+  stage(x + 0.5 * a.dt * d1, t + 0.5 * a.dt, ux + R(0.5) * h * a1, uy + R(0.5) * h * b1,
+        uz + R(0.5) * h * c1, d2, a2, b2, c2);
+  stage(x + 0.5 * a.dt * d2, t + 0.5 * a.dt, ux + R(0.5) * h * a2, uy + R(0.5) * h * b2,
+        uz + R(0.5) * h * c2, d3, a3, b3, c3);
+  stage(x + a.dt * d3, t + a.dt, ux + h * a3, uy + h * b3, uz + h * c3, d4, a4, b4, c4);
+  e.x += a.dt / 6.0 * (d1 + 2.0 * d2 + 2.0 * d3 + d4);
+  e.ux += h / R(6) * (a1 + R(2) * a2 + R(2) * a3 + a4);
+  e.uy += h / R(6) * (b1 + R(2) * b2 + R(2) * b3 + b4);
+  e.uz += h / R(6) * (c1 + R(2) * c2 + R(2) * c3 + c4);
+}
+
+template <typename R, int MODE>
+__global__ void k_track_rk4(TrackArgs a) {
+  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  TrackState<R> e{a.x[i], (R)a.ux[i], (R)a.uy[i], (R)a.uz[i], 0.f, 0.f, 0.f};
+  const R h = (R)a.dt, eps = (R)a.eps;
+  long long s = 0;
+  if (!may_overflow(a, e))
+    for (; s < a.steps - 1; ++s) rk4_step<R, MODE, false>(a, a.t0 + (double)s * a.dt, h, eps, e);
+  for (; s < a.steps; ++s) rk4_step<R, MODE, true>(a, a.t0 + (double)s * a.dt, h, eps, e);
+  a.x[i] = e.x;
+  a.ux[i] = e.ux;
+  a.uy[i] = e.uy;
+  a.uz[i] = e.uz;
 }
 
 // ---------------------------------------------------------------- self-check
