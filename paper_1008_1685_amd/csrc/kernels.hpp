@@ -5,6 +5,8 @@
 //               one thread per particle over cell-sorted SoA tiles; current
 //               accumulated in lane-private LDS copies of a window of nodes,
 //               then one global 64-bit atomic per node and work-group.
+//   k_step      for small runs: the fields of a step and the push of the next
+//               in one launch (its push tiles advance their own cells' fields).
 //   k_field     1D Yee advance (two B half steps around the E step), laser
 //               injection and absorption at the ends, Ex as the integral of
 //               the charge flux; one thread per node, halo recomputed.
@@ -141,8 +143,12 @@ struct PushArgs {
   // Cell range of every tile after the previous push (the particles' cells
   // now, as long as no sort or state change came between): with *pred_in
   // set, a tile sizes its current window from it instead of a pass over its
-  // cells.  Only a hint: a particle outside the window deposits by global
-  // atomics.  The push writes the next ranges and sets *pred_out.
+  // cells.  For a push by itself only a hint: a particle outside the window
+  // deposits by global atomics.  A fused step (k_step) gathers from the fields
+  // staged for this range, so there every particle must lie in it: the push
+  // before, of the same call and with at most a sort (which clears *pred_in)
+  // in between, has written it.  The push writes the next ranges and sets
+  // *pred_out.
   const int* rng_in;             // [tile][2] min, max
   int* rng_out;
   const int* pred_in;
@@ -312,7 +318,8 @@ __device__ __forceinline__ float rcp_rn_ge1(float x) {
 // exponent range and sort out special values: 7 and 4 more instructions of 17
 // and 11, some 40 of the 370 an average FP64 push issues.  Finite arguments
 // in [1, 2^1000] need none of it; infinities and NaN give NaN, which the
-// callers drop as they drop infinity (a momentum past 1e30).
+// pushes drop as they drop infinity (a momentum past 1e30); see rsq_any() for
+// tracked electrons.
 __device__ __forceinline__ double sqrt_rn_ge1(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   double s = x * y, h = 0.5 * y;
@@ -1334,8 +1341,8 @@ __global__ PIC_PUSH_BOUNDS void k_push_small(PushArgs<R>) {
 // push deposits into the next current buffer of three, and the field pass
 // clears the third.  A step of a small run is bound by the latency of its
 // launches, not by the few MB it moves: 12,800 particles in FP32 took 8.9 us
-// (push) + 4.5 us (fields) and a gap per step, now 9.3 us; 4e5 in FP64
-// 12.7 + 4.9, now 12.8 us.
+// (push) + 4.5 us (fields) and a gap per step, now 6.7 us in tiles of 256
+// particles (9.3 in tiles of 1,024); 4e5 in FP64 12.7 + 4.9, now 12.2 us.
 template <typename R>
 struct StepArgs {
   PushArgs<R> a;
@@ -2314,8 +2321,6 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
   return t;
 }
-
-__device__ __forceinline__ long long wave_sum_ll(long long v) { return wave_sum(v); }
 
 // LDS slots of the integer charge of a diagnostics tile
 constexpr int kDiagSlots = kSortWin + 1;

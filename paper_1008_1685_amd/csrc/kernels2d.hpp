@@ -7,11 +7,12 @@
 // Kernels:
 //   k_push2     gather -> Boris -> RR (electrons) -> 2D move -> fixed-point
 //               Esirkepov deposit, one thread per particle over cell-sorted
-//               tiles of 1,024.  A tile first stages the fields of its cells
-//               in LDS and gathers from there; each lane adds the non-zero
-//               terms of its particle's 3 x 3 stencil to one of several
-//               private copies of an LDS box covering the tile's cells; the
-//               box goes to HBM with one 64-bit atomic per node at the end.
+//               tiles of 256, 512 or 1,024.  A tile first stages the fields
+//               of its cells in LDS and gathers from there; each lane adds the
+//               non-zero terms of its particle's 3 x 3 stencil to one of
+//               several private copies of an LDS box covering the tile's cells;
+//               the box goes to HBM with one 64-bit atomic per node at the end.
+//               A tile whose box does not fit takes 256 particles at a time.
 //   k_field2    one Yee step (B half step, E step, B half step) per tile
 //               with halos recomputed in LDS, boundary guards, Poynting
 //               bookkeeping, the running integer charge implied by the
