@@ -492,7 +492,7 @@ struct MomentumOut {
 // p^(n) (the complete LL force, for tracking in given fields).  BX takes a
 // non-zero B_x (multi-dimensional grids); without it B_x = 0, as in 1D, and
 // none of its terms is evaluated.  ANY: momenta whose square overflows are
-// stepped too (the runs drop them after the step).
+// stepped too, without RR (the runs drop them after the step).
 template <typename R, bool RR, bool COMP, bool DERIV, bool BX = false, bool ANY = false>
 __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez, R by, R bz, R qh,
                                               R k, const FieldRates<R>& fr, float& rx, float& ry,
@@ -535,7 +535,7 @@ __device__ __forceinline__ void momentum_step(R ux, R uy, R uz, R ex, R ey, R ez
     // mid-step momentum (u_L + u^{n-1/2}) / 2 and its velocity
     const R qx = R(0.5) * (Lx + ux), qy = R(0.5) * (Ly + uy), qz = R(0.5) * (Lz + uz);
     const R g2 = R(1) + qx * qx + qy * qy + qz * qz;
-    const R ig = ANY ? rsq_any(g2) : rsq(g2);
+    const R ig = rsq(g2);
     const R vx = qx * ig, vy = qy * ig, vz = qz * ig;
     // F = E + v x B = -f_L
     const R Fx = ex + (vy * bz - vz * by);
@@ -1792,48 +1792,54 @@ struct TrackState {
   float rx, ry, rz;
 };
 
-// Whether an electron's squared momentum may overflow FP64 before its last
-// step.  From a moderate momentum only the RR force gets there, and the step
-// after is not finite in any form; so ANY (selects on the chain of every step:
-// 1.16 ms become 1.29 for 10,000 electrons and 2,000 steps, a check after each
-// step 1.24) is for the last step and for electrons that begin so (1.18).
 template <typename R>
-__device__ __forceinline__ bool may_overflow(const TrackArgs& a, const TrackState<R>& e) {
-  const double kick = (fabs(a.ay) + fabs(a.az)) * fmax(1.0, fabs(a.dt));
-  return sizeof(R) == 8 && !(fabs(e.ux) + fabs(e.uy) + fabs(e.uz) < 1e140 && kick < 1e100);
+__device__ __forceinline__ TrackState<R> track_start(const TrackArgs& a, long long i) {
+  return {a.x[i], (R)a.ux[i], (R)a.uy[i], (R)a.uz[i], 0.f, 0.f, 0.f};
+}
+
+// Whether an electron was lost to a momentum whose square overflows FP64 (or
+// began so): the short roots give NaN there.  It is then tracked again in the
+// form that allows for it (ANY), whose selects on the chain of every step
+// would take 1.16 ms to 1.29 for 10,000 electrons and 2,000 steps.
+template <typename R>
+__device__ __forceinline__ bool track_lost(const TrackState<R>& e) {
+  return sizeof(R) == 8 && !(e.x == e.x && e.ux == e.ux && e.uy == e.uy && e.uz == e.uz);
 }
 
 // The paper's leapfrog scheme: x^n and u^{n-1/2} in, x^{n+steps} and
 // u^{n+steps-1/2} out; the position advances in FP64 by dt u_x / gamma.
 // MODE: 0 Lorentz only, 1 with f_R of Eq. (f_r), 2 with the complete force.
 template <typename R, int MODE, bool ANY>
-__device__ __forceinline__ void leapfrog_step(const TrackArgs& a, double t, R qh, R k, TrackState<R>& e) {
+__device__ __forceinline__ void leapfrog(const TrackArgs& a, TrackState<R>& e) {
   constexpr bool COMP = sizeof(R) == 4 && MODE > 0;
+  const R qh = (R)(-0.5 * a.dt), k = (R)(a.eps * a.dt);
   float stiff = 0.f;
-  R ey, ez;
-  FieldRates<R> fr;
-  wave_at<R>(a, e.x, t, ey, ez, fr);
-  MomentumOut<R> o;
-  momentum_step<R, (MODE > 0), COMP, (MODE == 2), false, ANY>(e.ux, e.uy, e.uz, R(0), ey, ez, -ez, ey, qh, k, fr,
-                                                              e.rx, e.ry, e.rz, stiff, o);
-  e.ux = o.nx;
-  e.uy = o.ny;
-  e.uz = o.nz;
-  const double gx = (double)e.ux + e.rx, gy = (double)e.uy + e.ry, gz = (double)e.uz + e.rz;
-  const double g2 = 1.0 + gx * gx + gy * gy + gz * gz;
-  e.x += a.dt * gx * (ANY ? rsq_any(g2) : rsq(g2));
+  for (long long s = 0; s < a.steps; ++s) {
+    R ey, ez;
+    FieldRates<R> fr;
+    wave_at<R>(a, e.x, a.t0 + (double)s * a.dt, ey, ez, fr);
+    MomentumOut<R> o;
+    momentum_step<R, (MODE > 0), COMP, (MODE == 2), false, ANY>(e.ux, e.uy, e.uz, R(0), ey, ez, -ez, ey, qh, k, fr,
+                                                                e.rx, e.ry, e.rz, stiff, o);
+    e.ux = o.nx;
+    e.uy = o.ny;
+    e.uz = o.nz;
+    const double gx = (double)e.ux + e.rx, gy = (double)e.uy + e.ry, gz = (double)e.uz + e.rz;
+    const double g2 = 1.0 + gx * gx + gy * gy + gz * gz;
+    e.x += a.dt * gx * (ANY ? rsq_any(g2) : rsq(g2));
+  }
 }
 
 template <typename R, int MODE>
 __global__ void k_track_leapfrog(TrackArgs a) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  TrackState<R> e{a.x[i], (R)a.ux[i], (R)a.uy[i], (R)a.uz[i], 0.f, 0.f, 0.f};
-  const R qh = (R)(-0.5 * a.dt), k = (R)(a.eps * a.dt);
-  long long s = 0;
-  if (!may_overflow(a, e))
-    for (; s < a.steps - 1; ++s) leapfrog_step<R, MODE, false>(a, a.t0 + (double)s * a.dt, qh, k, e);
-  for (; s < a.steps; ++s) leapfrog_step<R, MODE, true>(a, a.t0 + (double)s * a.dt, qh, k, e);
+  TrackState<R> e = track_start<R>(a, i);
+  leapfrog<R, MODE, false>(a, e);
+  if (track_lost(e)) {
+    e = track_start<R>(a, i);
+    leapfrog<R, MODE, true>(a, e);
+  }
   a.x[i] = e.x;
   a.ux[i] = (double)e.ux + e.rx;
   a.uy[i] = (double)e.uy + e.ry;
@@ -1905,12 +1911,13 @@ template <typename R, int MODE>
 __global__ void k_track_rk4(TrackArgs a) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  TrackState<R> e{a.x[i], (R)a.ux[i], (R)a.uy[i], (R)a.uz[i], 0.f, 0.f, 0.f};
+  TrackState<R> e = track_start<R>(a, i);
   const R h = (R)a.dt, eps = (R)a.eps;
-  long long s = 0;
-  if (!may_overflow(a, e))
-    for (; s < a.steps - 1; ++s) rk4_step<R, MODE, false>(a, a.t0 + (double)s * a.dt, h, eps, e);
-  for (; s < a.steps; ++s) rk4_step<R, MODE, true>(a, a.t0 + (double)s * a.dt, h, eps, e);
+  for (long long s = 0; s < a.steps; ++s) rk4_step<R, MODE, false>(a, a.t0 + (double)s * a.dt, h, eps, e);
+  if (MODE == 0 && track_lost(e)) {  // (with RR no form of an overflowed stage is finite)
+    e = track_start<R>(a, i);
+    for (long long s = 0; s < a.steps; ++s) rk4_step<R, MODE, true>(a, a.t0 + (double)s * a.dt, h, eps, e);
+  }
   a.x[i] = e.x;
   a.ux[i] = e.ux;
   a.uy[i] = e.uy;

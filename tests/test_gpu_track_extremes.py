@@ -26,3 +26,24 @@ def test_overflowing_momentum(u, scheme):
             assert np.array_equal(np.delete(g, 2, 0), np.delete(r, 2, 0)), c
         assert got[0][2] == x[2] and got[1][2, c] == u
         assert np.all(np.isfinite(got[1][2]))
+
+
+def test_overflow_by_the_radiation_force():
+    # an explicit RR step far past its stability squares a momentum: in the
+    # step that takes its square past the largest number the electron stays
+    # in place, and keeps its finite momentum if that was the last step
+    from paper_1008_1685_amd.track import track
+
+    print("\n[gpu] track, RR overflow", flush=True)
+    n = 200
+    x, u = np.linspace(0, 1, n), np.zeros((n, 3))
+    u[:, 0] = -np.logspace(60, 110, n)
+    kw = dict(a_y=350.0, scheme="leapfrog", rr="reduced", precision="fp64", dt=0.01)
+    seen = 0
+    for steps in range(1, 4):
+        x0, _ = track(x, u, steps=steps - 1, **kw)
+        x1, u1 = track(x, u, steps=steps, **kw)
+        hit = np.all(np.isfinite(u1), 1) & (np.max(np.abs(u1), 1) > 1.4e154)
+        assert np.array_equal(x1[hit], x0[hit]), steps
+        seen += int(hit.sum())
+    assert seen > 0
