@@ -505,6 +505,8 @@ def write_traffic(fetch, write, cfetch, cwrite, out_path, kernel="k_push", workl
 
     def kib(path, name, last=50):
         rows = [r for r in csv.DictReader(open(path)) if name in r["Kernel_Name"]]
+        if not rows:
+            raise SystemExit(f"{path} holds no launch of {name}")
         rows.sort(key=lambda r: int(r["Dispatch_Id"]))
         return float(np.mean([float(r["Counter_Value"]) for r in rows][-last:])), len(rows)
 
@@ -563,7 +565,7 @@ def main():
             if path == os.path.join(ROOT, "profiles", "traffic.json"):
                 path = os.path.join(ROOT, "profiles", "traffic_d2.json")
             write_traffic(*args.write_traffic, path, kernel="k_push2", workload="d2",
-                          match="k_push2<float>", last=400)
+                          match="k_push2<float", last=400)  # (any tile)
         else:
             write_traffic(*args.write_traffic, args.traffic_json)
         return

@@ -84,6 +84,26 @@ def test_traffic_record_from_counter_files(tmp_path):
     assert bench.stored_traffic(str(out), "c3", "k_push") is None
 
 
+def test_traffic_record_of_the_2d_push(tmp_path, monkeypatch):
+    # the 2D push is instantiated by tile: its launches are found whichever it
+    # is, and files without any are refused instead of recorded
+    gib_kib = 2 ** 30 / 1024
+    name = "void pic::k_push2<float, 4>(pic::Push2Args<float>)"
+    files = [str(tmp_path / f) for f in ("f.csv", "w.csv", "cf.csv", "cw.csv")]
+    _counter_file(files[0], name, "FETCH_SIZE", [5.0] * 10 + [1000.0] * 400)
+    _counter_file(files[1], name, "WRITE_SIZE", [7.0] * 10 + [2000.0] * 400)
+    _counter_file(files[2], "__amd_rocclr_copyBuffer", "FETCH_SIZE", [gib_kib / 2] * 4)
+    _counter_file(files[3], "__amd_rocclr_copyBuffer", "WRITE_SIZE", [gib_kib] * 4)
+    out = tmp_path / "t.json"
+    monkeypatch.setattr(sys, "argv", ["bench.py", "--traffic-json", str(out), "--traffic-2d", "--write-traffic", *files])
+    bench.main()
+    t = json.load(open(out))
+    assert t["launches_averaged"] == 400 and t["bytes_per_launch"] == pytest.approx(4000.0 * 1024)
+    _counter_file(files[0], "void pic::k_field2s<float>()", "FETCH_SIZE", [1.0])
+    with pytest.raises(SystemExit, match="no launch"):
+        bench.main()
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
